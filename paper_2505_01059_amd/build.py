@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmtp.so")
 
-SOURCES = ["kernels.hip", "rollout_quad.hip", "rollout_seg.hip", "plan.cpp", "batch.hip", "batch.cpp", "server.cpp", "plant.cpp", "noalloc.hip",
+SOURCES = ["kernels.hip", "rollout_quad.hip", "rollout_seg.hip", "rollout_wide.hip", "plan.cpp", "batch.hip", "batch.cpp", "server.cpp", "plant.cpp", "noalloc.hip",
            "schedule_cache.cpp"]
 # The batched persistent kernel, the quad-lane and the time-sliced pair-lane
 # rollouts run one wave per SIMD, and LLVM's iterative ILP scheduler orders their
@@ -19,6 +19,7 @@ SOURCES = ["kernels.hip", "rollout_quad.hip", "rollout_seg.hip", "plan.cpp", "ba
 EXTRA_FLAGS = {
     "batch.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
     "rollout_quad.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
+    "rollout_wide.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
     "rollout_seg.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
 }
 HIP_FLAGS = [

@@ -198,10 +198,10 @@ constexpr size_t kOnePerUnitLds = 96 * 1024;
 
 // LDS of a rollout launch that also draws tensor-path controls: the candidate
 // tile's arrays over the whole horizon, at least kOnePerUnitLds.
-static size_t gen_lds_bytes(const PlanDesc& P) {
-  const size_t tile = sizeof(float) * static_cast<size_t>(cand_dyn_floats(P.L, P.W, P.T < kTChunk ? P.T : kTChunk));
-  return tile > kOnePerUnitLds ? tile : kOnePerUnitLds;
+static size_t gen_tile_bytes(const PlanDesc& P) {
+  return sizeof(float) * static_cast<size_t>(cand_dyn_floats(P.L, P.W, P.T < kTChunk ? P.T : kTChunk));
 }
+static size_t gen_lds_bytes(const PlanDesc& P) { return std::max(gen_tile_bytes(P), kOnePerUnitLds); }
 
 template <bool ONE>
 static hipError_t launch_rollout_kernel(const PlanDesc& P, dim3 grid, size_t lds, hipStream_t st);
@@ -211,17 +211,19 @@ static hipError_t launch_rollout_kernel(const PlanDesc& P, dim3 grid, size_t lds
 static hipError_t launch_rollout(const PlanDesc& P0, hipStream_t st, int gen_k) {
   PlanDesc P = P0;
   if (is_pair_chain(P.dyn, P.n_links) && P.seg_ctl != nullptr && P.seg_grid > 0) return launch_rollout_seg(P, st);
-  P.roll_blocks = rollout_blocks(P);
+  const int lanes = wide_lanes(P);
+  P.roll_blocks = lanes > 0 ? wide_blocks(P, lanes) : rollout_blocks(P);
   P.gen_k = gen_k;
   int blocks = P.roll_blocks;
   size_t lds = 0;
-  if (gen_k >= 0 && P.U2 != nullptr && P.gen_grid > P.roll_blocks) {
-    blocks = P.gen_grid;
-    lds = gen_lds_bytes(P);
-  } else if (P.roll_blocks < P.gen_grid) {
+  if (gen_k >= 0 && P.U2 != nullptr) {
+    blocks = std::max(P.gen_grid, P.roll_blocks + kMinGenBlocks);
+    lds = blocks <= P.gen_grid ? gen_lds_bytes(P) : gen_tile_bytes(P);
+  } else if (P.roll_blocks <= P.gen_grid) {
     lds = kOnePerUnitLds;
   }
   const dim3 grid(blocks);
+  if (lanes > 0) return launch_rollout_wide(P, lanes, grid, lds, st, blocks <= P.gen_grid);
   // a launch with LDS reserved holds one workgroup per unit
   return lds != 0 ? launch_rollout_kernel<true>(P, grid, lds, st) : launch_rollout_kernel<false>(P, grid, lds, st);
 }

@@ -28,6 +28,13 @@ hipError_t launch_iteration_stage(const PlanDesc& P, int stage, int k, int k0, i
 // Quad-lane chain rollout (rollout_quad.hip); one: the launch holds one
 // workgroup per compute unit.
 hipError_t launch_rollout_quad(const PlanDesc& P, dim3 grid, size_t lds, hipStream_t st, bool one);
+// Workgroups that a drawing-ahead rollout launch adds at least.
+constexpr int kMinGenBlocks = 32;
+// Wide rollout forms (rollout_wide.hip): the lanes per candidate a plan's
+// launch takes (0: its narrow form), the workgroups and the launch itself.
+int wide_lanes(const PlanDesc& P);
+int wide_blocks(const PlanDesc& P, int lanes);
+hipError_t launch_rollout_wide(const PlanDesc& P, int lanes, dim3 grid, size_t lds, hipStream_t st, bool one);
 // Time-sliced pair-lane rollout (rollout_seg.hip): epoch bump, then the
 // persistent launch of P.seg_grid workgroups.
 hipError_t launch_rollout_seg(const PlanDesc& P, hipStream_t st);

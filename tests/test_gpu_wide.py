@@ -1,0 +1,68 @@
+"""Wide rollout forms: a single plan whose launch would leave compute units
+idle spreads each candidate over more lanes and runs its randomised models side
+by side; the batched launch keeps one or two lanes per candidate and runs the
+models in turn.  Both do the same operations in the same order, so the last
+iteration's costs, the refit and the action agree bit for bit."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import mtp_workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _uneven(cfg):
+    rng = np.random.default_rng(cfg.seed + 1000)
+    lengths = rng.uniform(0.7, 1.3, cfg.n_links).astype(np.float32)
+    return cfg.replace(task=dataclasses.replace(cfg.task, lengths=lengths))
+
+
+def _chain(n, total, T=19, **k):
+    return W.chain_config(name=f"w{n}_{total}", n_links=n, interp=W.BSPLINE, n_tensor=total - total // 9,
+                          n_gauss=total // 9, horizon=T, n_layers=5, n_width=7, n_elites=8, n_iters=2, seed=total, **k)
+
+
+def _contact(n, total, T=41, R=1, **k):
+    # the ground just under the base: every candidate touches it
+    return W.chain_contact_config(name=f"k{n}_{total}_r{R}", n_links=n, n_tensor=total - total // 9,
+                                  n_gauss=total // 9, horizon=T, n_layers=5, n_width=7, n_elites=8, n_iters=2,
+                                  seed=total + R, ground_y=-0.02, n_replicas=R, **k)
+
+
+CASES = [
+    # four lanes over 4 links; two lanes (the most that fit) and the first size past them
+    _chain(4, 101), _chain(4, 14337), _chain(4, 28673),
+    # 12 links on four lanes: a lone candidate group, a partly filled last workgroup, the last size that fits
+    _chain(12, 10), _chain(12, 1000), _chain(12, 14336), _chain(12, 14337),
+    # 24 links: eight lanes, the last size they fit, four lanes beyond
+    _chain(24, 33), _chain(24, 7168, T=9), _chain(24, 7169, T=9), _uneven(_chain(24, 500)), _uneven(_chain(12, 500)),
+    # contact on one to four lanes; on eight and four lanes per candidate
+    _contact(4, 77), _contact(7, 203), _contact(7, 14500), _contact(24, 70), _contact(24, 7300, T=30),
+    _uneven(_contact(24, 300)),
+    # randomised models side by side: few, as many as a workgroup holds, more than that, and more work than units
+    _contact(7, 190, R=3), _contact(4, 40, R=63), _contact(4, 40, R=64), _contact(24, 60, R=33, T=12),
+    _contact(24, 3000, R=2, T=24), _contact(7, 25000, R=3, T=12), _contact(24, 15000, R=3, T=6),
+]
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
+def test_wide_rollout_equals_batched(cfg):
+    import torch
+    import paper_2505_01059_amd as mtp
+    x0 = W.initial_state(cfg, seed=5)
+    print(f"[wide] {cfg.name}: {cfg.n_samples} candidates, {cfg.n_links} links", flush=True)
+    plan = mtp.Plan(cfg, device="cuda:0")
+    plan.replan(x0, shift=1, replan_idx=0)
+    bt = mtp.Batch([cfg], device="cuda:0")
+    bt.replan(bt.pack_x0([x0]), shift=1)
+    want = bt.actions()[0]
+    torch.cuda.synchronize()
+    a, b = plan.buffers(), bt.buffers(0)
+    assert plan.flags() & 6 == 0
+    for key in ("cost", "elite_idx", "mu", "sigma"):
+        assert np.array_equal(a[key].cpu().numpy(), b[key].cpu().numpy()), key
+    assert np.array_equal(plan.action(), want)
+    plan.close()
+    bt.close()
