@@ -314,7 +314,10 @@ mtp_status mtp_batch_set_state(mtp_batch* b, int32_t i, const float* d_mu, const
  *                  split_pct % of the persistent workgroups runs the finest items
  *                  instead (one joint of one candidate tile, one rollout tile, four
  *                  refit outputs), so that a light load still spreads over the chip;
- *                  0 = never, 100 = fewer tiles than workgroups
+ *                  0 = never, 100 = fewer tiles than workgroups.  Unless 0, an
+ *                  instance whose own stages take longer in turn than most of the
+ *                  launch's work per workgroup also runs the finest items, with
+ *                  more lanes per candidate in its rollout
  * Defaults: {0, 1, 1, 1, 64, 100}.
  */
 typedef struct {

@@ -41,6 +41,44 @@ uint32_t items_for(const mtp_config& c, int k_begin, int k_end, uint32_t shape) 
   return 1u + per_iter * static_cast<uint32_t>(k_end - k_begin);
 }
 
+// Items of a launch's iterations for queue sizing: the finest shape with the
+// widest rollout tiles.
+uint32_t most_items(const mtp_config& c) {
+  return items_for(c, 0, c.n_iters, kShapeFinest | make_shape(0, 0, 0, 0, max_wide_lg(c.dynamics, c.n_links)));
+}
+
+// Estimated times (us) of one workgroup in the stages of one CEM iteration
+// under an item shape, measured on full and on light launches: a rollout tile
+// per step, a candidate tile per joint and step, a refit output per wave.
+struct StageCost {
+  double path;   // from the first item to the last, with a workgroup for every item
+  double work;   // sum over all items
+};
+
+StageCost stage_cost(const mtp_config& c, uint32_t shape, int workgroups) {
+  const int B = c.n_tensor + c.n_gauss, n = c.ctrl_dim, T = c.horizon;
+  const bool quad = is_quad_chain(c.dynamics, c.n_links), pair = is_pair_chain(c.dynamics, c.n_links);
+  const bool contact = c.dynamics == MTP_DYN_CHAIN_CONTACT;
+  double step = 0.75;                                               // point mass
+  if (quad) step = 0.86;
+  else if (pair) step = (contact ? 0.18 : 0.16) * c.n_links;
+  else if (c.dynamics != MTP_DYN_POINT_MASS) step = (contact ? 0.45 : 0.3) * c.n_links;
+  constexpr double kWide[3] = {1.0, 0.66, 0.5};
+  step *= kWide[shape_wide_lg(shape)] * (c.n_replicas > 1 ? c.n_replicas : 1) * (1 << shape_roll_lg(shape));
+  const int joints = shape_cand_joint(shape) ? 1 : n;
+  const double item[5] = {1.0, (1 << shape_cand_lg(shape)) * joints * (3.0 + 0.095 * T), 4.0 + step * T,
+                          16.0 + B / 2000.0, 0.6 * (1 << shape_upd_lg(shape))};
+  constexpr double kItem = 1.5;   // queue, fences and waiting per item
+  StageCost s{0.0, 0.0};
+  for (uint32_t ph = kPhPaths; ph <= kPhUpd; ++ph) {
+    const uint32_t items = phase_items(B, c.n_tensor, T, n, ph, quad, pair, c.sample_wor != 0, shape);
+    const double t = item[ph - kPhPaths] + kItem;
+    s.work += items * t;
+    s.path += ((items + workgroups - 1) / workgroups) * t;
+  }
+  return s;
+}
+
 uint32_t log2_of(int v) {
   uint32_t l = 0;
   while ((1 << (l + 1)) <= v) ++l;
@@ -78,7 +116,7 @@ bool batch_layout(const mtp_config* cfgs, int32_t n, BatchLayout* L, std::string
       return false;
     }
     L->lays.push_back(compute_layout(cfgs[i]));
-    L->capacity += items_for(cfgs[i], 0, cfgs[i].n_iters, kShapeFinest);   // sized for the most items
+    L->capacity += most_items(cfgs[i]);
     L->x0_total += cfgs[i].state_dim;
     L->act_total += cfgs[i].ctrl_dim;
   }
@@ -517,7 +555,6 @@ mtp_status mtp_batch_step(mtp_batch* b, int32_t n_active, const int32_t* h_activ
   if (b->staged_pending) BCHK(b, hipEventSynchronize(b->staged), "staging wait");
   b->staged_pending = false;
   std::vector<char> seen(b->n, 0);
-  uint32_t total = 0;
   int x0_off = 0;
   std::vector<int32_t> x0_offsets(b->n);
   std::vector<int32_t> act_offsets(b->n);
@@ -575,16 +612,44 @@ mtp_status mtp_batch_step(mtp_batch* b, int32_t n_active, const int32_t* h_activ
   }
   const bool light = cand_tiles * 100u < static_cast<uint64_t>(b->sched.split_pct) * static_cast<uint64_t>(b->grid);
   const uint32_t shape = light ? kShapeFinest : coarse_shape(b->sched);
-  for (int a = 0; a < n_active; ++a) {
-    const int i = h_active[a];
-    b->h_ictl[i].shape = shape;
-    total += items_for(b->cfgs[i], h_k_begin[a], h_k_end[a], shape);
+  // The launch cannot end before its longest instance, whose stages run one
+  // after another: an instance whose own path is more than kPathShare of the
+  // launch's work per workgroup takes finer items, then wide rollout tiles
+  // (shorter, at more work in total), until it is not.  0.7 measured best of
+  // 0.5, 0.7 and 1 over 8 to 32 uneven instances (the queue makes every
+  // instance wait its turn, so a path as long as the whole work is already
+  // too long); launches with more work keep the plain shape.
+  constexpr double kPathShare = 0.7;
+  std::vector<uint32_t> shapes(n_active, shape);
+  if (b->sched.split_pct > 0) {
+    double work = 0.0;
+    for (int a = 0; a < n_active; ++a)
+      work += (h_k_end[a] - h_k_begin[a]) * stage_cost(b->cfgs[h_active[a]], shape, b->grid).work;
+    const double limit = kPathShare * work / b->grid;
+    for (int a = 0; a < n_active; ++a) {
+      const mtp_config& c = b->cfgs[h_active[a]];
+      const int iters = h_k_end[a] - h_k_begin[a];
+      const uint32_t widest = max_wide_lg(c.dynamics, c.n_links);
+      for (uint32_t lg = 0; lg <= widest && iters * stage_cost(c, shapes[a], b->grid).path > limit; ++lg)
+        shapes[a] = kShapeFinest | make_shape(0, 0, 0, 0, lg);
+    }
   }
+  auto count = [&]() {
+    uint64_t sum = 0;
+    for (int a = 0; a < n_active; ++a) sum += items_for(b->cfgs[h_active[a]], h_k_begin[a], h_k_end[a], shapes[a]);
+    return sum;
+  };
+  uint64_t total = count();
+  if (total > b->lay.capacity) {   // a queue sized by its owner: the plain shape needs the fewest items of those chosen
+    shapes.assign(n_active, shape);
+    total = count();
+  }
+  for (int a = 0; a < n_active; ++a) b->h_ictl[h_active[a]].shape = shapes[a];
   if (total > b->lay.capacity) {
     b->err = "step needs more queue items than the batch was sized for";
     return MTP_ERR_INVALID_ARG;
   }
-  return run_launch(b, n_active, total, d_x0_packed);
+  return run_launch(b, n_active, static_cast<uint32_t>(total), d_x0_packed);
 }
 
 mtp_status mtp_batch_replan(mtp_batch* b, const float* d_x0_packed, const int32_t* h_shift) {

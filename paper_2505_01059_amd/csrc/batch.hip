@@ -15,6 +15,7 @@
 // and every reduction has an order fixed by the instance alone, so a result
 // does not depend on which workgroup ran which tile or on the other instances.
 #include "batch.hpp"
+#include "rollout_wide.hpp"
 
 namespace mtp {
 
@@ -28,7 +29,6 @@ union BatchSmem {
   CandSmem cand;
   TopkSmem topk;
   EntropySmem ent;
-  PointMassSmem pm;
 };
 
 struct BatchShared {
@@ -39,54 +39,106 @@ struct BatchShared {
   int32_t abort;
 };
 
-__device__ __forceinline__ void run_rollout_tile(const PlanDesc& P, uint32_t tile, BatchSmem& sm) {
-  const int b = static_cast<int>(tile) * kBatchThreads + static_cast<int>(threadIdx.x);
-  if (P.dyn == kPointMass) {
-    stage_obstacles(P, sm.pm);
-    __syncthreads();
-    if (b < P.B) rollout_point_mass_any<1>(P, b, 0, sm.pm);
-    return;
+// One rollout tile of each form, out of line (the descriptor is read again from
+// its uniform address).  Inlined into the one persistent kernel, the forms
+// shared a single register allocation, so that a change in one of them moved
+// the others' times by 3 to 5 %, and more forms did not fit: 256 uneven
+// instances 82.0 ms per replan inlined, 81.6 ms out of line.
+__device__ __forceinline__ PlanDesc load_desc(const PlanDesc* desc) {
+  const uint64_t a = reinterpret_cast<uint64_t>(desc);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a));
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a >> 32));
+  return *reinterpret_cast<const PlanDesc*>(static_cast<uint64_t>(hi) << 32 | lo);
+}
+
+template <int N, bool CONTACT, bool EQ>
+__device__ __noinline__ void roll_chain_tile(const PlanDesc* desc, uint32_t tile) {
+  const PlanDesc P = load_desc(desc);
+  tile = __builtin_amdgcn_readfirstlane(tile);
+  const int t = static_cast<int>(threadIdx.x);
+  if constexpr (!CONTACT && quad_chain_links<N>()) {
+    const int b = static_cast<int>(tile) * (kBatchThreads / 4) + (t >> 2);
+    if (b < P.B) rollout_chain_quad<N>(P, b, t & 3);
+  } else if constexpr (pair_chain_links<N>()) {
+    const int b = static_cast<int>(tile) * (kBatchThreads / 2) + (t >> 1);
+    if (b < P.B) rollout_chain_pair<N, CONTACT, EQ>(P, b, (t & 1) != 0);
+  } else {
+    const int b = static_cast<int>(tile) * kBatchThreads + t;
+    if (b < P.B) rollout_chain<N, CONTACT>(P, b);
   }
-  if (is_quad_chain(P.dyn, P.n_links)) {
-    const int bq = static_cast<int>(tile) * (kBatchThreads / 4) + static_cast<int>(threadIdx.x >> 2);
-    if (bq >= P.B) return;
-    switch (P.n_links) {
-#define X(N) case N: if constexpr (quad_chain_links<N>()) rollout_chain_quad<N>(P, bq, threadIdx.x & 3); return;
-      MTP_CHAIN_LINKS(X)
-#undef X
-      default: return;
-    }
+}
+
+// The same tile on a wide form, 2^LG times the narrow lanes per candidate.
+template <int N, bool CONTACT, bool EQ, int LG>
+__device__ __noinline__ void roll_wide_tile(const PlanDesc* desc, uint32_t tile) {
+  const PlanDesc P = load_desc(desc);
+  tile = __builtin_amdgcn_readfirstlane(tile);
+  constexpr bool kPair = pair_chain_links<N>();
+  constexpr int kLanes = (kPair ? 2 : 1) << LG;
+  constexpr int kWriter = kPair ? kLanes / 2 - 1 : kLanes - 1;
+  const int t = static_cast<int>(threadIdx.x), pos = t % kLanes;
+  const int bb = static_cast<int>(tile) * (kBatchThreads / kLanes) + t / kLanes;
+  const bool live = bb < P.B;
+  const int b = live ? bb : P.B - 1;   // idle groups shadow the last candidate and store nothing
+  float total = 0.0f;
+  for (int rep = 0; rep < P.R; ++rep) {
+    if constexpr (kPair) total += rollout_half<N, (1 << LG), CONTACT, EQ>(P, b, pos, rep, live);
+    else total += rollout_line<N, kLanes, CONTACT>(P, b, pos, rep, live);
   }
-  if (is_pair_chain(P.dyn, P.n_links)) {
-    const int bp = static_cast<int>(tile) * (kBatchThreads / 2) + static_cast<int>(threadIdx.x >> 1);
-    if (bp >= P.B) return;
-    const bool lane_b = (threadIdx.x & 1) != 0;
-    if (P.dyn == kChain) {
-      switch (P.n_links) {
-#define X(N) case N: if constexpr (pair_chain_links<N>()) rollout_chain_pair<N, false>(P, bp, lane_b); return;
-        MTP_CHAIN_LINKS(X)
-#undef X
-        default: return;
+  if (live && pos == kWriter) P.cost[b] = finite_or_inf(P.R == 1 ? total : total / static_cast<float>(P.R));
+}
+
+template <int N, bool CONTACT>
+__device__ __forceinline__ void roll_chain(const PlanDesc* desc, bool eq, uint32_t lg, uint32_t tile) {
+  constexpr uint32_t kMaxLg = max_wide_lg(CONTACT ? kChainContact : kChain, N);
+  if constexpr (pair_chain_links<N>()) {
+    if constexpr (kMaxLg >= 1) {
+      if (lg == 1u) {
+        if (eq) roll_wide_tile<N, CONTACT, true, 1>(desc, tile);
+        else roll_wide_tile<N, CONTACT, false, 1>(desc, tile);
+        return;
       }
     }
-    switch (P.n_links) {
-#define X(N) case N: if constexpr (pair_chain_links<N>()) rollout_chain_pair<N, true>(P, bp, lane_b); return;
-      MTP_CONTACT_LINKS(X)
-#undef X
-      default: return;
+    if constexpr (kMaxLg >= 2) {
+      if (lg == 2u) {
+        if (eq) roll_wide_tile<N, CONTACT, true, 2>(desc, tile);
+        else roll_wide_tile<N, CONTACT, false, 2>(desc, tile);
+        return;
+      }
     }
+    if (eq) roll_chain_tile<N, CONTACT, true>(desc, tile);
+    else roll_chain_tile<N, CONTACT, false>(desc, tile);
+  } else {
+    if constexpr (kMaxLg >= 2) {
+      if (lg == 1u) { roll_wide_tile<N, CONTACT, false, 1>(desc, tile); return; }
+      if (lg == 2u) { roll_wide_tile<N, CONTACT, false, 2>(desc, tile); return; }
+    }
+    roll_chain_tile<N, CONTACT, false>(desc, tile);
   }
-  if (b >= P.B) return;
+}
+
+__device__ __noinline__ void roll_point_mass_tile(const PlanDesc* desc, uint32_t tile) {
+  __shared__ PointMassSmem pm;
+  const PlanDesc P = load_desc(desc);
+  const int b = static_cast<int>(__builtin_amdgcn_readfirstlane(tile)) * kBatchThreads + static_cast<int>(threadIdx.x);
+  stage_obstacles(P, pm);
+  __syncthreads();
+  if (b < P.B) rollout_point_mass_any<1>(P, b, 0, pm);
+}
+
+__device__ __forceinline__ void run_rollout_tile(const PlanDesc* desc, const PlanDesc& P, uint32_t lg, uint32_t tile) {
+  if (P.dyn == kPointMass) { roll_point_mass_tile(desc, tile); return; }
+  const bool eq = P.eq_len != 0;
   if (P.dyn == kChain) {
     switch (P.n_links) {
-#define X(N) case N: if constexpr (!pair_chain_links<N>() && !quad_chain_links<N>()) rollout_chain<N, false>(P, b); return;
+#define X(N) case N: roll_chain<N, false>(desc, eq, lg, tile); return;
       MTP_CHAIN_LINKS(X)
 #undef X
       default: return;
     }
   }
   switch (P.n_links) {
-#define X(N) case N: if constexpr (!pair_chain_links<N>()) rollout_chain<N, true>(P, b); return;
+#define X(N) case N: roll_chain<N, true>(desc, eq, lg, tile); return;
     MTP_CONTACT_LINKS(X)
 #undef X
     default: return;
@@ -175,7 +227,7 @@ __global__ __launch_bounds__(kBatchThreads, MTP_BATCH_MIN_WG_PER_CU) void k_batc
       }
       case kPhRoll:
         // an item is 2^roll_lg consecutive rollout tiles, one per pass
-        run_rollout_tile(P, (tile << shape_roll_lg(shape)) + sub, sm);
+        run_rollout_tile(descs + inst, P, shape_wide_lg(shape), (tile << shape_roll_lg(shape)) + sub);
         break;
       case kPhTopk:
         topk_block<kBatchThreads>(P, sm.topk);
@@ -202,7 +254,7 @@ __global__ __launch_bounds__(kBatchThreads, MTP_BATCH_MIN_WG_PER_CU) void k_batc
     if (phase == kPhRoll) {
       const uint32_t lg = shape_roll_lg(shape);
       const uint32_t next = (tile << lg) + sub + 1u;
-      if (sub + 1u < (1u << lg) && next < phase_tiles(P, kPhRoll, 0u)) {
+      if (sub + 1u < (1u << lg) && next < phase_tiles(P, kPhRoll, shape & ~make_shape(0, 0, 3, 0))) {
         ++sub;   // the same item's next tile (the barrier above ordered its LDS reuse)
         continue;
       }

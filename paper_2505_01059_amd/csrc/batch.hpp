@@ -18,17 +18,27 @@ enum : uint32_t { kPhShift = 0, kPhPaths = 1, kPhCand = 2, kPhRoll = 3, kPhTopk 
 //   bit  2    a candidate item covers one joint of its tiles instead of all
 //   bits 3-4  log2 of the rollout tiles (one workgroup's candidates each) per item
 //   bits 5-7  log2 of the refit outputs (t, j) per item, 2..6
+//   bits 8-9  log2 of the rollout's lanes per candidate over the narrow form's
+//             (0: one, two or four lanes by model; 1, 2: wide forms, see
+//             rollout_wide.hpp), at most max_wide_lg of the model
 // The shape changes only which workgroup computes what: every candidate,
 // rollout and refit output is computed by the same code from the same inputs.
 __host__ __device__ constexpr uint32_t make_shape(uint32_t cand_lg, uint32_t cand_joint, uint32_t roll_lg,
-                                                  uint32_t upd_lg) {
-  return cand_lg | (cand_joint << 2) | (roll_lg << 3) | (upd_lg << 5);
+                                                  uint32_t upd_lg, uint32_t wide_lg = 0) {
+  return cand_lg | (cand_joint << 2) | (roll_lg << 3) | (upd_lg << 5) | (wide_lg << 8);
 }
 __host__ __device__ constexpr uint32_t shape_cand_lg(uint32_t s) { return s & 3u; }
 __host__ __device__ constexpr uint32_t shape_cand_joint(uint32_t s) { return (s >> 2) & 1u; }
 __host__ __device__ constexpr uint32_t shape_roll_lg(uint32_t s) { return (s >> 3) & 3u; }
 __host__ __device__ constexpr uint32_t shape_upd_lg(uint32_t s) { return (s >> 5) & 7u; }
-// The most items: one joint of one candidate tile, one rollout tile and four
+__host__ __device__ constexpr uint32_t shape_wide_lg(uint32_t s) { return (s >> 8) & 3u; }
+// Widest rollout form of a model in the batched kernel (log2 over the narrow one).
+__host__ __device__ constexpr uint32_t max_wide_lg(int dyn, int n_links) {
+  if (is_pair_chain(dyn, n_links)) return n_links % 8 == 0 ? 2u : (n_links % 4 == 0 ? 1u : 0u);
+  if (dyn == kChainContact || (dyn == kChain && n_links >= 4 && !is_quad_chain(dyn, n_links))) return 2u;
+  return 0u;
+}
+// The most items on narrow rollouts: one joint of one candidate tile, one rollout tile and four
 // refit outputs (one per wave) per item.  Queues are sized for this shape.
 constexpr uint32_t kShapeFinest = make_shape(0, 1, 0, 2);
 // The shape of loaded launches unless a schedule says otherwise: a candidate
@@ -53,7 +63,7 @@ __host__ __device__ inline uint32_t phase_items(int B, int P, int T, int n, uint
       return ((tiles + per - 1u) / per) * (shape_cand_joint(shape) ? static_cast<uint32_t>(n) : 1u);
     }
     case kPhRoll: {
-      const int cands = quad ? kBatchThreads / 4 : (pair ? kBatchThreads / 2 : kBatchThreads);
+      const int cands = (quad ? kBatchThreads / 4 : (pair ? kBatchThreads / 2 : kBatchThreads)) >> shape_wide_lg(shape);
       const uint32_t tiles = static_cast<uint32_t>((B + cands - 1) / cands);
       const uint32_t per = 1u << shape_roll_lg(shape);
       return (tiles + per - 1u) / per;

@@ -1605,11 +1605,11 @@ __device__ __forceinline__ void pair_start(const PlanDesc& P, const PairConsts<N
 
 // One candidate b per lane pair; B is the tip-half lane.  Both lanes of a pair
 // must run this together.
-template <int N, bool CONTACT>
+template <int N, bool CONTACT, bool EQ = false>
 __device__ __forceinline__ void rollout_chain_pair(const PlanDesc& P, int b, bool B) {
   static_assert(N >= 10 && N % 2 == 0, "pair-lane chain needs an even link count >= 10");
   constexpr int M = N / 2;
-  PairConsts<N> K;
+  PairConsts<N, EQ> K;
   pair_setup<N, CONTACT>(P, B, K);
   // randomised models: the candidate's cost is the mean over R rollouts
   const int R = CONTACT ? P.R : 1;

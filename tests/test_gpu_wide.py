@@ -1,7 +1,8 @@
 """Wide rollout forms: a single plan whose launch would leave compute units
 idle spreads each candidate over more lanes and runs its randomised models side
-by side; the batched launch keeps one or two lanes per candidate and runs the
-models in turn.  Both do the same operations in the same order, so the last
+by side; the batched launch keeps one or two lanes per candidate (schedules that
+never split), or takes the wide forms for its longest instances, and runs the
+models in turn.  All do the same operations in the same order, so the last
 iteration's costs, the refit and the action agree bit for bit."""
 import dataclasses
 
@@ -55,14 +56,17 @@ def test_wide_rollout_equals_batched(cfg):
     print(f"[wide] {cfg.name}: {cfg.n_samples} candidates, {cfg.n_links} links", flush=True)
     plan = mtp.Plan(cfg, device="cuda:0")
     plan.replan(x0, shift=1, replan_idx=0)
-    bt = mtp.Batch([cfg], device="cuda:0")
-    bt.replan(bt.pack_x0([x0]), shift=1)
-    want = bt.actions()[0]
     torch.cuda.synchronize()
-    a, b = plan.buffers(), bt.buffers(0)
+    a = plan.buffers()
     assert plan.flags() & 6 == 0
-    for key in ("cost", "elite_idx", "mu", "sigma"):
-        assert np.array_equal(a[key].cpu().numpy(), b[key].cpu().numpy()), key
-    assert np.array_equal(plan.action(), want)
+    for split in (0, 100):
+        bt = mtp.Batch([cfg], device="cuda:0")
+        bt.set_schedule(split_pct=split)
+        bt.replan(bt.pack_x0([x0]), shift=1)
+        want = bt.actions()[0]
+        b = bt.buffers(0)
+        for key in ("cost", "elite_idx", "mu", "sigma"):
+            assert np.array_equal(a[key].cpu().numpy(), b[key].cpu().numpy()), (key, split)
+        assert np.array_equal(plan.action(), want)
+        bt.close()
     plan.close()
-    bt.close()
