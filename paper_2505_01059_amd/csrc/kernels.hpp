@@ -28,6 +28,8 @@ hipError_t launch_iteration_stage(const PlanDesc& P, int stage, int k, int k0, i
 // Quad-lane chain rollout (rollout_quad.hip); one: the launch holds one
 // workgroup per compute unit.
 hipError_t launch_rollout_quad(const PlanDesc& P, dim3 grid, size_t lds, hipStream_t st, bool one);
+// Lanes per candidate that the decision to draw ahead counts for a point mass.
+constexpr int kPmOverlapLanes = 8;
 // Workgroups that a drawing-ahead rollout launch adds at least.
 constexpr int kMinGenBlocks = 32;
 // Wide rollout forms (rollout_wide.hip): the lanes per candidate a plan's
