@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmtp.so")
 
-SOURCES = ["kernels.hip", "rollout_quad.hip", "rollout_seg.hip", "rollout_wide.hip", "plan.cpp", "batch.hip", "batch.cpp", "server.cpp", "plant.cpp", "noalloc.hip",
+SOURCES = ["kernels.hip", "rollout_quad.hip", "rollout_seg.hip", "rollout_wide.hip", "pm_replan.hip", "plan.cpp", "batch.hip", "batch.cpp", "server.cpp", "plant.cpp", "noalloc.hip",
            "schedule_cache.cpp"]
 # The batched persistent kernel, the quad-lane and the time-sliced pair-lane
 # rollouts run one wave per SIMD, and LLVM's iterative ILP scheduler orders their

@@ -40,6 +40,8 @@ hipError_t launch_rollout_wide(const PlanDesc& P, int lanes, dim3 grid, size_t l
 // Time-sliced pair-lane rollout (rollout_seg.hip): epoch bump, then the
 // persistent launch of P.seg_grid workgroups.
 hipError_t launch_rollout_seg(const PlanDesc& P, hipStream_t st);
+// A whole point-mass replan (pm_replan.hip) from start state x0_src.
+hipError_t launch_pm_replan(const PlanDesc& P, uint32_t r, int shift, const float* x0_src, hipStream_t st);
 // Workgroups of the (not time-sliced) rollout kernel of a plan.
 int rollout_blocks(const PlanDesc& P);
 // Grid and segment count of the time-sliced pair-lane rollout for the current

@@ -80,7 +80,17 @@ struct PlanDesc {
   int32_t gen_spec;      // this generator launch draws for replan ctrl[0] + 1, iteration 0, leaving Z and I
   int32_t cand_skip;     // this candidate launch leaves the tensor paths when ctrl[4] is set
   int32_t gen_grid;      // compute units: workgroups of such a launch (one per unit)
+  float* pm_cost;        // [K][P] tensor-path costs of every iteration (whole point-mass replans, or null)
 };
+
+// Sizes that a whole point-mass replan (pm_replan.hip) holds on one compute unit.
+constexpr int kPmGraph = 2048;       // graph values L * W * 2
+constexpr int kPmSteps = 256;        // horizon
+constexpr int kPmNormals = 6400;     // normals 2 T (G - 1) of an iteration's local samples
+constexpr int kPmLocal = 32;         // local candidates
+constexpr int kPmElites = 64;        // one per lane of a wave
+constexpr int kPmValues = 9216;      // elite controls 2 T E
+constexpr int kPmCands = 1024;       // candidates
 
 // ------------------------------------------------------------------ Philox
 // Philox4x32-10 from Salmon et al., SC'11: ten rounds of two 32x32->64-bit

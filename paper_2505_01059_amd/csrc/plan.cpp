@@ -3,6 +3,7 @@
 // the C ABI declared in include/mtp.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -156,6 +157,8 @@ Layout compute_layout(const mtp_config& c, bool plan) {
   L.seg_state = L.segmented ? take((n + n / 2 + 1) * groups * 64 * 4) : 0;
   L.overlap = plan && uses_gen_overlap(c);
   L.U2 = L.overlap ? take(T * n * L.ldU * 4) : 0;
+  L.pm = plan && uses_pm_replan(c);
+  L.pm_cost = L.pm ? take(static_cast<size_t>(c.n_iters) * std::max(c.n_tensor, 1) * 4) : 0;
   L.transient = off;
   L.total = L.resident + L.transient;
   return L;
@@ -279,6 +282,7 @@ void mtp::set_transient(PlanDesc* P, const mtp_config& c, const Layout& L, uint8
   P->X = c.n_debug_states > 0 ? reinterpret_cast<float*>(tb + L.X) : nullptr;
   P->seg_state = L.segmented ? reinterpret_cast<float*>(tb + L.seg_state) : nullptr;
   P->U2 = L.overlap ? reinterpret_cast<float*>(tb + L.U2) : nullptr;
+  P->pm_cost = L.pm ? reinterpret_cast<float*>(tb + L.pm_cost) : nullptr;
 }
 
 bool mtp::uses_gen_overlap(const mtp_config& c) {
@@ -302,6 +306,22 @@ bool mtp::uses_segmented_rollout(const mtp_config& c) {
                     (c.n_links % 2) == 0;
   const int R = c.n_replicas > 1 ? c.n_replicas : 1;
   return pair && R == 1 && (B + 31) / 32 > kSimds && c.horizon >= 16;
+}
+
+// Few enough local samples for one workgroup's rollout tile, and everything it
+// keeps within its LDS.  The bound on the elites' controls is also where the
+// one workgroup's refit takes what the launches cost (us per replan, staged and
+// whole, 6 iterations of about 1000 candidates: 2 T E = 10000 153 and 151 to
+// 154, 13184 164 and 175, 16384 163 and 181; obstacle counts do not matter: 256
+// obstacles 206 and 177).  More local samples shared out over workgroups, with
+// the costs exchanged between them, took longer than the staged kernels (3341
+// candidates, 340 local: 158 staged, 194).  Drawing without replacement, the
+// cost entropy and recorded states stay with the staged kernels.
+bool mtp::uses_pm_replan(const mtp_config& c) {
+  return c.dynamics == MTP_DYN_POINT_MASS && !c.sample_wor && !(c.diagnostics & 1) && c.n_debug_states == 0 &&
+         static_cast<long long>(c.n_tensor) + c.n_gauss <= kPmCands && c.n_gauss <= kPmLocal &&
+         c.n_elites <= kPmElites && c.horizon <= kPmSteps && 2 * c.horizon * c.n_elites <= kPmValues &&
+         2 * c.horizon * (c.n_gauss - 1) <= kPmNormals && 2 * c.n_layers * c.n_width <= kPmGraph;
 }
 
 // The S in 4..16 whose unit count groups*S is closest above to a whole number
@@ -584,6 +604,11 @@ mtp_status mtp_replan_at(mtp_plan* p, const float* d_x0, int32_t shift_steps, ui
   if (d_x0 == nullptr) return set_err(p, MTP_ERR_INVALID_ARG, "d_x0 is NULL");
   if (shift_steps < 0) return set_err(p, MTP_ERR_INVALID_ARG, "shift_steps must be >= 0");
   const bool graph = p->use_graph && !p->timing;
+  if (graph && p->lay.pm) {
+    HIPCHK(p, launch_pm_replan(p->P, replan_idx, shift_steps, d_x0, p->stream), "point-mass replan");
+    p->next_r = replan_idx + 1;
+    return MTP_OK;
+  }
   if (graph) {
     const mtp_status s = ensure_graph(p);
     if (s != MTP_OK) return s;

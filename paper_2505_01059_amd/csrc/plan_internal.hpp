@@ -20,9 +20,10 @@ namespace mtp {
 struct Layout {
   size_t ldU;
   size_t ctrl, x0, mu, sigma, tmp, action, basis, span, task, sparams, entropy, seg_ctl, seg_done;   // resident
-  size_t Z, I, U, cost, eidx, ecost, w, X, seg_state, U2;                                   // transient
+  size_t Z, I, U, cost, eidx, ecost, w, X, seg_state, U2, pm_cost;                          // transient
   bool segmented;   // the rollout is time-sliced (see uses_segmented_rollout)
   bool overlap;     // second U buffer: next tensor paths drawn during the rollout (see uses_gen_overlap)
+  bool pm;          // whole point-mass replans (see uses_pm_replan)
   size_t resident, transient;
   size_t total;   // resident + transient
 };
@@ -50,6 +51,8 @@ bool uses_segmented_rollout(const mtp_config& c);
 // own beside it) or a rollout that leaves at least 32 of the 256 compute units
 // free (drawn by workgroups the rollout launch adds).
 bool uses_gen_overlap(const mtp_config& c);
+// Whether a single plan's graph-mode replans run as the two kernels of pm_replan.hip.
+bool uses_pm_replan(const mtp_config& c);
 // Segments of the time-sliced rollout for a given number of resident waves.
 int segment_count(int groups, int resident_waves);
 // Rounds of the without-replacement path permutation: 2 L ceil(log2 W).

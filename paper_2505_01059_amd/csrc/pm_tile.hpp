@@ -15,6 +15,7 @@
 namespace mtp {
 
 constexpr int kTileSteps = 64;   // steps of a tile held in LDS at a time
+constexpr int kTileBlock = 8;    // steps per block of the serial passes
 
 template <int C>
 struct PmTile {
@@ -62,21 +63,36 @@ __device__ __forceinline__ float pm_tile_cost(const PlanDesc& P, PmTile<C>& sm, 
     const int steps = min(kTileSteps, P.T - t0);
     gen(t0, steps);
     __syncthreads();
+    // both serial passes go by whole blocks of steps, the next block's values
+    // loading while the current one's are used; the steps past the end of the
+    // last block are integrated and ignored, and their cost terms are zero
+    const int blocks = (steps + kTileBlock - 1) / kTileBlock;
     if (tid < 2 * C) {
-#pragma unroll 16
-      for (int i = 0; i < steps; ++i) {
-        vel = fmaf(dt, sm.u[i][dim][cand], vel);
-        pos = fmaf(dt, vel, pos);
-        sm.p[i][dim][cand] = pos;
-        rec(t0 + i, dim, cand, pos, vel);
+      float cu[kTileBlock], nu[kTileBlock];
+#pragma unroll
+      for (int i = 0; i < kTileBlock; ++i) cu[i] = sm.u[i][dim][cand];
+      for (int b = 0; b < blocks; ++b) {
+        const int i0 = b * kTileBlock, i1 = min(b + 1, blocks - 1) * kTileBlock;
+#pragma unroll
+        for (int i = 0; i < kTileBlock; ++i) nu[i] = sm.u[i1 + i][dim][cand];
+#pragma unroll
+        for (int i = 0; i < kTileBlock; ++i) {
+          vel = fmaf(dt, cu[i], vel);
+          pos = fmaf(dt, vel, pos);
+          sm.p[i0 + i][dim][cand] = pos;
+          if (i0 + i < steps) rec(t0 + i0 + i, dim, cand, pos, vel);
+        }
+#pragma unroll
+        for (int i = 0; i < kTileBlock; ++i) cu[i] = nu[i];
       }
     }
     __syncthreads();
-    if (tid < steps * C) {
+    const int points = blocks * kTileBlock * C;
+    if (tid < points) {
       float px[R], py[R], g[R][8];
 #pragma unroll
       for (int q = 0; q < R; ++q) {
-        const int i = min((tid + q * BS) / C, steps - 1), c = (tid + q * BS) % C;
+        const int i = min((tid + q * BS) / C, kTileSteps - 1), c = (tid + q * BS) % C;
         px[q] = sm.p[i][0][c];
         py[q] = sm.p[i][1][c];
 #pragma unroll
@@ -100,21 +116,31 @@ __device__ __forceinline__ float pm_tile_cost(const PlanDesc& P, PmTile<C>& sm, 
 #pragma unroll
       for (int q = 0; q < R; ++q) {
         const int at = tid + q * BS;
-        if (at < steps * C) {
+        if (at < points) {
           const int i = at / C, c = at % C;
           const float obst = ((g[q][0] + g[q][1]) + (g[q][2] + g[q][3])) + ((g[q][4] + g[q][5]) + (g[q][6] + g[q][7]));
           const float dx = px[q] - gx, dy = py[q] - gy;
           const float ux = sm.u[i][0][c], uy = sm.u[i][1][c];
           float v = fmaf(wg, fmaf(dx, dx, dy * dy), obst);
           v = fmaf(wu, fmaf(ux, ux, uy * uy), v);
-          sm.c[i][c] = v;
+          sm.c[i][c] = i < steps ? v : 0.0f;
         }
       }
     }
     __syncthreads();
     if (tid < C) {
-#pragma unroll 16
-      for (int i = 0; i < steps; ++i) cost += sm.c[i][tid];
+      float cc[kTileBlock], nc[kTileBlock];
+#pragma unroll
+      for (int i = 0; i < kTileBlock; ++i) cc[i] = sm.c[i][tid];
+      for (int b = 0; b < blocks; ++b) {
+        const int i1 = min(b + 1, blocks - 1) * kTileBlock;
+#pragma unroll
+        for (int i = 0; i < kTileBlock; ++i) nc[i] = sm.c[i1 + i][tid];
+#pragma unroll
+        for (int i = 0; i < kTileBlock; ++i) cost += cc[i];
+#pragma unroll
+        for (int i = 0; i < kTileBlock; ++i) cc[i] = nc[i];
+      }
     }
   }
   return finite_or_inf(cost);
