@@ -66,7 +66,7 @@ StageCost stage_cost(const mtp_config& c, uint32_t shape, int workgroups) {
   constexpr double kWide[3] = {1.0, 0.66, 0.5};
   step *= kWide[shape_wide_lg(shape)] * (c.n_replicas > 1 ? c.n_replicas : 1) * (1 << shape_roll_lg(shape));
   const int joints = shape_cand_joint(shape) ? 1 : n;
-  const double item[5] = {1.0, (1 << shape_cand_lg(shape)) * joints * (3.0 + 0.095 * T), 4.0 + step * T,
+  const double item[5] = {1.0, (1 << shape_cand_lg(shape)) * (6.0 + joints * (1.0 + 0.057 * T)), 4.0 + step * T,
                           16.0 + B / 2000.0, 0.6 * (1 << shape_upd_lg(shape))};
   constexpr double kItem = 1.5;   // queue, fences and waiting per item
   StageCost s{0.0, 0.0};

@@ -15,6 +15,7 @@
 // and every reduction has an order fixed by the instance alone, so a result
 // does not depend on which workgroup ran which tile or on the other instances.
 #include "batch.hpp"
+#include "batch_cand.hpp"
 #include "rollout_wide.hpp"
 
 namespace mtp {
@@ -26,7 +27,7 @@ __device__ __forceinline__ uint32_t phase_tiles(const PlanDesc& P, uint32_t phas
 
 union BatchSmem {
   PathSmem path;
-  CandSmem cand;
+  BatchCandSmem cand;
   TopkSmem topk;
   EntropySmem ent;
 };
@@ -210,7 +211,6 @@ __global__ __launch_bounds__(kBatchThreads, MTP_BATCH_MIN_WG_PER_CU) void k_batc
         // an item is 2^cand_lg consecutive candidate tiles with all their
         // joints, or one joint of them
         const uint32_t r = P.ctrl[0];
-        const CandView v = cand_view(sm.cand);
         const bool one_joint = shape_cand_joint(shape) != 0u;
         const int group = one_joint ? static_cast<int>(tile) / P.n : static_cast<int>(tile);
         const int j0 = one_joint ? static_cast<int>(tile) - group * P.n : 0;
@@ -218,11 +218,10 @@ __global__ __launch_bounds__(kBatchThreads, MTP_BATCH_MIN_WG_PER_CU) void k_batc
         const int per = 1 << shape_cand_lg(shape);
         const int n_tiles = (P.B + kCandThreads - 1) / kCandThreads;
         const int ct1 = min(group * per + per, n_tiles);
-        for (int ct = group * per; ct < ct1; ++ct)
-          for (int j = j0; j < j1; ++j) {
-            cand_tile(P, r, static_cast<int>(k), j, ct * kCandThreads, 0, P.T, v);
-            __syncthreads();
-          }
+        for (int ct = group * per; ct < ct1; ++ct) {
+          batch_cand_tile(P, r, static_cast<int>(k), j0, j1, ct * kCandThreads, sm.cand);
+          __syncthreads();
+        }
         break;
       }
       case kPhRoll:

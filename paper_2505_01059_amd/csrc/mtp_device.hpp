@@ -217,18 +217,8 @@ constexpr float kTwoPiSq = 39.47841760435743f;
 // store the path indices I.
 constexpr int kTChunk = 128;   // horizon steps whose tables are staged in LDS at a time
 
-struct CandSmem {
-  float z[kMaxLayers * kMaxWidth];                // Z[l][w] for this joint
-  float ctrl[kMaxLayers][kCandThreads];          // per-thread control points
-  float slope[kMaxLayers][kCandThreads];         // per-thread Akima slopes (unit spacing)
-  float tb[kTChunk * kBasisStride];              // spline weights of the staged steps
-  int32_t ts[kTChunk];                           // their span / interval index
-  float tmu[kTChunk], tsg[kTChunk];              // mean and std of joint j at those steps
-};
-
-// The candidate tile's LDS arrays, either the fixed-size struct above or a
-// block sized for one plan (L*W graph column, L control points and slopes per
-// thread, `chunk` staged steps).
+// The candidate tile's LDS arrays, in a block sized for one plan (L*W graph
+// column, L control points and slopes per thread, `chunk` staged steps).
 struct CandView {
   float* z;        // [L*W]
   float* ctrl;     // [L][kCandThreads]
@@ -239,13 +229,6 @@ struct CandView {
   float* tsg;      // [chunk]
   int chunk;
 };
-
-__device__ __forceinline__ CandView cand_view(CandSmem& sm) {
-  CandView v;
-  v.z = sm.z; v.ctrl = &sm.ctrl[0][0]; v.slope = &sm.slope[0][0]; v.tb = sm.tb; v.ts = sm.ts;
-  v.tmu = sm.tmu; v.tsg = sm.tsg; v.chunk = kTChunk;
-  return v;
-}
 
 __host__ __device__ constexpr int cand_dyn_floats(int L, int W, int chunk) {
   return L * W + 2 * L * kCandThreads + chunk * (kBasisStride + 3);
