@@ -172,12 +172,52 @@ __global__ __launch_bounds__(kUpdThreads) void k_refit_regen(PlanDesc P, int k, 
   regen_elites(P, k, tq, j, sm);
   if (t < P.T) {
     float mn, sn;
-    update_output_from(P, t * P.n + j, [&](int e) { return sm.vals[c][e]; }, &mn, &sn);
+    update_output_from(P, t * P.n + j, gptr(P.w), [&](int e) { return sm.vals[c][e]; }, &mn, &sn);
     if ((threadIdx.x & 63) == 0) { mom[c][0] = mn; mom[c][1] = sn; }
   }
   if constexpr (NEXT) {
     __syncthreads();
     local_store<kUpdThreads>(P, P.U2, tq, j, k_next, r, z, mom);
+  }
+}
+
+// Top-E selection and refit of an iteration in one launch, one workgroup per
+// four steps of a joint.  Every workgroup selects the elites for itself (the
+// same values in each; the first stores them), then four of its waves refit one
+// step each, as k_update, or k_update_next with NEXT.  The selection is one
+// workgroup's latency either way, and one launch less is a microsecond per
+// iteration.  Replans in two launches -> one: 561 candidates x 3 links x 4
+// iterations 165.0 -> 162.1 us; 9216 x 7 x 8 1.020 -> 1.002 ms; 3376 x 12 x 6
+// 0.631 -> 0.621 ms; 3341 point masses x 6 153.3 -> 146.2 us; 13500 x 4 x 4 0.310
+// -> 0.303 ms.
+constexpr int kFusedThreads = kTopkThreads;
+template <bool NEXT>
+__global__ __launch_bounds__(kFusedThreads) void k_select_refit(PlanDesc P, int k_next) {
+  __shared__ TopkSmem sm;
+  __shared__ float mom[4][2];
+  const int tq = static_cast<int>(blockIdx.x) / P.n, j = static_cast<int>(blockIdx.x) - tq * P.n;
+  const int c = static_cast<int>(threadIdx.x) >> 6;
+  const int t = 4 * tq + c;
+  const uint32_t r = P.ctrl[0];
+  float z[kLocalKeep][4];
+  if constexpr (NEXT) local_normals<kFusedThreads>(P, tq, j, k_next, r, z);
+  if (P.gen_spec && blockIdx.x == 0 && threadIdx.x == 0) {   // as k_update
+    P.ctrl[3] = P.ctrl[0] + 1u;
+    P.ctrl[5] = 1u;
+  }
+  topk_block<kFusedThreads, true>(P, sm, blockIdx.x == 0);
+  if (c < 4 && t < P.T) {
+    const int o = t * P.n + j;
+    const auto row = gptr(P.U) + static_cast<size_t>(o) * static_cast<size_t>(P.ldU);
+    const float* w = topk_weights(sm);
+    const int* elite = topk_elites(sm);
+    float mn, sn;
+    update_output_from(P, o, w, [&](int e) { return row[elite[e]]; }, &mn, &sn);
+    if ((threadIdx.x & 63) == 0) { mom[c][0] = mn; mom[c][1] = sn; }
+  }
+  if constexpr (NEXT) {
+    __syncthreads();
+    local_store<kFusedThreads>(P, P.U2, tq, j, k_next, r, z, mom);
   }
 }
 
@@ -351,6 +391,16 @@ hipError_t launch_stage(const PlanDesc& P, int stage, int k, hipStream_t st) {
   }
 }
 
+static bool is_sliced(const PlanDesc& P) {
+  return is_pair_chain(P.dyn, P.n_links) && P.seg_ctl != nullptr && P.seg_grid > 0;
+}
+
+// the plan's layout assumed a 256-unit chip; a device without a free unit
+// beyond the rollout's workgroups runs the plain sequence
+static bool draws_ahead(const PlanDesc& P) {
+  return P.U2 != nullptr && (is_sliced(P) || P.gen_grid > rollout_blocks(P));
+}
+
 // Stage `stage` of iteration k within a run of iterations [k0, k1).  With the
 // overlap (P.U2 set) iteration k works on U (k1 - 1 - k even, so the last
 // iteration always ends in U) or U2 (odd); its rollout also draws iteration
@@ -361,11 +411,8 @@ hipError_t launch_stage(const PlanDesc& P, int stage, int k, hipStream_t st) {
 // paths do not depend on the sampling distribution.
 hipError_t launch_iteration_stage(const PlanDesc& P, int stage, int k, int k0, int k1, hipStream_t st,
                                   const SideLane* side) {
-  // the plan's layout assumed a 256-unit chip; a device without a free unit
-  // beyond the rollout's workgroups runs the plain sequence
-  const bool sliced = is_pair_chain(P.dyn, P.n_links) && P.seg_ctl != nullptr && P.seg_grid > 0;
-  const bool overlap = P.U2 != nullptr && (sliced || P.gen_grid > rollout_blocks(P));
-  if (!overlap) return launch_stage(P, stage, k, st);
+  if (!draws_ahead(P)) return launch_stage(P, stage, k, st);
+  const bool sliced = is_sliced(P);
   PlanDesc Pk = P;
   if ((k1 - 1 - k) & 1) { Pk.U = P.U2; Pk.U2 = P.U; }
   // a whole replan of a plan that draws across replans: iteration 0 may take
@@ -426,6 +473,31 @@ hipError_t launch_iteration_stage(const PlanDesc& P, int stage, int k, int k0, i
     }
     default: return launch_stage(Pk, stage, k, st);
   }
+}
+
+// Stages 2 and 3 of iteration k in one launch where every workgroup of
+// k_select_refit has a compute unit of its own (its LDS admits one per unit, so a
+// second round would select once more) and the costs fit that LDS.
+static bool fuses_refit(const PlanDesc& P) {
+  return (P.diag & 1) == 0 && P.B <= kTopkCache && ((P.T + 3) / 4) * P.n <= P.gen_grid &&
+         !refit_regenerates(P.interp, P.p, P.wor, P.E, P.B);
+}
+
+hipError_t launch_iteration(const PlanDesc& P, int k, int k0, int k1, hipStream_t st, const SideLane* side) {
+  const bool fused = fuses_refit(P);
+  for (int stage = 0; stage < (fused ? 2 : 4); ++stage) {
+    const hipError_t e = launch_iteration_stage(P, stage, k, k0, k1, st, side);
+    if (e != hipSuccess) return e;
+  }
+  if (!fused) return hipSuccess;
+  const bool ahead = draws_ahead(P), last = k + 1 >= k1;
+  PlanDesc Pk = P;
+  if (ahead && ((k1 - 1 - k) & 1)) { Pk.U = P.U2; Pk.U2 = P.U; }
+  Pk.gen_spec = (ahead && last && P.spec && k0 == 0 && k1 == P.K) ? 1 : 0;
+  const int tiles = ((P.T + 3) / 4) * P.n;
+  if (ahead && !last) k_select_refit<true><<<tiles, kFusedThreads, 0, st>>>(Pk, k + 1);
+  else k_select_refit<false><<<tiles, kFusedThreads, 0, st>>>(Pk, -1);
+  return hipGetLastError();
 }
 
 hipError_t gen_configure(PlanDesc* P) {

@@ -25,6 +25,9 @@ struct SideLane {
 // side is null).
 hipError_t launch_iteration_stage(const PlanDesc& P, int stage, int k, int k0, int k1, hipStream_t st,
                                   const SideLane* side = nullptr);
+// The four stages of iteration k in that run, selection and refit in one launch
+// where that is the faster.
+hipError_t launch_iteration(const PlanDesc& P, int k, int k0, int k1, hipStream_t st, const SideLane* side = nullptr);
 // Quad-lane chain rollout (rollout_quad.hip); one: the launch holds one
 // workgroup per compute unit.
 hipError_t launch_rollout_quad(const PlanDesc& P, dim3 grid, size_t lds, hipStream_t st, bool one);

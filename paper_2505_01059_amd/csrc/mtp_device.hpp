@@ -1796,6 +1796,12 @@ struct TopkSmem {
   uint32_t wlo[kTopkThreads / 64], whi[kTopkThreads / 64];
 };
 
+// The elites' weights and indices after topk_block, in the image cache (free by
+// then; selection is over).
+static_assert(2 * kMaxElites <= kTopkCache, "weights and indices fit the image cache");
+__device__ __forceinline__ float* topk_weights(TopkSmem& sm) { return reinterpret_cast<float*>(sm.cache); }
+__device__ __forceinline__ int* topk_elites(TopkSmem& sm) { return reinterpret_cast<int*>(sm.cache) + kMaxElites; }
+
 // All BS threads find the digit whose bin holds the rank-th key (1-based) of
 // hist[0..nbins): each thread owns a run of consecutive bins, a wave scan and
 // the wave totals give every run's offset, and the one thread whose run holds
@@ -2113,8 +2119,10 @@ __device__ __forceinline__ const unsigned long long* topk_select(const PlanDesc&
   return ord;
 }
 
-template <int BS>
-__device__ __forceinline__ void topk_block(const PlanDesc& P, TopkSmem& sm) {
+// KEEP: the elites' weights and indices stay in LDS (topk_weights, topk_elites)
+// for the refit of this workgroup, and only a `writer` workgroup stores them.
+template <int BS, bool KEEP = false>
+__device__ __forceinline__ void topk_block(const PlanDesc& P, TopkSmem& sm, bool writer = true) {
   const auto cost = gptr(P.cost);
   const int tid = threadIdx.x;
   const int B = P.B, E = P.E;
@@ -2122,7 +2130,7 @@ __device__ __forceinline__ void topk_block(const PlanDesc& P, TopkSmem& sm) {
   __syncthreads();
   // elites, costs and softmax weights w_e = exp(-(s_e - s_0)/lambda) / sum;
   // the unnormalised weights wait in LDS (the image cache is free by now)
-  float* wbuf = reinterpret_cast<float*>(sm.cache);
+  float* wbuf = topk_weights(sm);
   // elite costs come back from their keys' images; +inf (also NaN) and zero
   // (also -0) are read from memory to keep the cost as it was
   auto elite_cost = [&](unsigned long long key, int idx) -> float {
@@ -2137,8 +2145,11 @@ __device__ __forceinline__ void topk_block(const PlanDesc& P, TopkSmem& sm) {
     if (uidx >= static_cast<uint32_t>(B)) { uidx = 0u; atomicOr(&P.ctrl[2], 2u); }   // never expected
     const int idx = static_cast<int>(uidx);
     const float ce = elite_cost(ord[e], idx);
-    gptr(P.eidx)[e] = idx;
-    gptr(P.ecost)[e] = ce;
+    if constexpr (KEEP) topk_elites(sm)[e] = idx;
+    if (writer) {
+      gptr(P.eidx)[e] = idx;
+      gptr(P.ecost)[e] = ce;
+    }
     wbuf[e] = uniform ? 1.0f : expf(-(ce - s0) / P.lam);
   }
   // normalisation sum in an order fixed by E alone (independent of the block
@@ -2152,8 +2163,13 @@ __device__ __forceinline__ void topk_block(const PlanDesc& P, TopkSmem& sm) {
   }
   __syncthreads();
   const float inv = 1.0f / sm.red[0];
-  for (int e = tid; e < E; e += BS) gptr(P.w)[e] = wbuf[e] * inv;
-  if (tid == 0 && !(s0 < INFINITY)) atomicOr(&P.ctrl[2], 1u);
+  for (int e = tid; e < E; e += BS) {
+    const float we = wbuf[e] * inv;
+    if constexpr (KEEP) wbuf[e] = we;
+    if (writer) gptr(P.w)[e] = we;
+  }
+  if (writer && tid == 0 && !(s0 < INFINITY)) atomicOr(&P.ctrl[2], 1u);
+  if constexpr (KEEP) __syncthreads();
 }
 
 // Iteration k_next's candidates that depend on the refitted distribution, at
@@ -2292,12 +2308,12 @@ __device__ __forceinline__ void entropy_block(const PlanDesc& P, int k, EntropyS
 constexpr int kUpdKeep = 16;
 
 // Refits output o = (t, j); every lane returns the new mean and std, lane 0 stores them.
-// The refit of output o from the elites' controls val(e) (e < E), in a fixed
-// order: weighted mean, weighted variance about it, sigma floor, smoothing.
-template <class Val>
-__device__ __forceinline__ void update_output_from(const PlanDesc& P, int o, Val val, float* mu_new, float* sg_new) {
+// The refit of output o from the elites' controls val(e) (e < E), with
+// weights w[e] in a fixed order: weighted mean, weighted variance about it, sigma floor, smoothing.
+template <class Weights, class Val>
+__device__ __forceinline__ void update_output_from(const PlanDesc& P, int o, Weights w, Val val, float* mu_new,
+                                                   float* sg_new) {
   const int lane = threadIdx.x & 63;
-  const auto w = gptr(P.w);
   // the old moments do not depend on the elite values: their loads go out first
   const auto mu = gptr(P.mu), sigma = gptr(P.sigma);
   const float mu_old = mu[o], sg_old = sigma[o];
@@ -2353,7 +2369,7 @@ __device__ __forceinline__ void update_output(const PlanDesc& P, int o, float* m
                                               float* sg_new = nullptr) {
   const auto row = gptr(P.U) + static_cast<size_t>(o) * static_cast<size_t>(P.ldU);
   const auto eidx = gptr(P.eidx);
-  update_output_from(P, o, [&](int e) { return row[eidx[e]]; }, mu_new, sg_new);
+  update_output_from(P, o, gptr(P.w), [&](int e) { return row[eidx[e]]; }, mu_new, sg_new);
 }
 
 // Elite controls drawn again instead of gathered.  The gather reads one value

@@ -439,11 +439,10 @@ mtp_status mtp::upload_plan_tables(const mtp_config& c, const PlanDesc& P, const
 }
 
 hipError_t mtp::enqueue_iterations(const PlanDesc& P, int k_begin, int k_end, hipStream_t st, const SideLane* side) {
-  for (int k = k_begin; k < k_end; ++k)
-    for (int stage = 0; stage < 4; ++stage) {
-      const hipError_t e = launch_iteration_stage(P, stage, k, k_begin, k_end, st, side);
-      if (e != hipSuccess) return e;
-    }
+  for (int k = k_begin; k < k_end; ++k) {
+    const hipError_t e = launch_iteration(P, k, k_begin, k_end, st, side);
+    if (e != hipSuccess) return e;
+  }
   return hipSuccess;
 }
 
