@@ -1780,7 +1780,8 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum_u32(uint32_t v) {
 
 constexpr int kTopkBins = 2048;      // radix digits of up to 11 bits
 constexpr int kTopkCache = 16384;    // batches up to this size keep their cost images in LDS
-constexpr int kTopkRankSort = 1024;  // elite sets up to this size are ordered by counting ranks
+constexpr int kTopkRankSort = 1024;  // elite sets up to this size are ordered by ranks
+constexpr int kTopkRunSort = 256;    // larger sets are ordered by runs of 64
 constexpr int kTopkBoundary = 256;   // a boundary bin this small is ordered by counting ranks
 
 struct TopkSmem {
@@ -1872,6 +1873,51 @@ __device__ __forceinline__ void topk_rank(const unsigned long long* src, int n, 
   }
 }
 
+// Orders the n distinct keys src[0..n) (n <= kTopkRankSort) into src, by way of
+// runs[]: each run of 64 is ordered by counting, then a key's rank is the sum of
+// its positions in all runs, found by bisection (eight runs' reads in flight).
+// Work n (64 + 7 n / 64) instead of the n^2 of counting every key against every
+// other.  Counting -> runs: 1000 keys 29 -> 7 us, 512 keys 8.0 -> 3.4 us, 384
+// keys 4.7 -> 3.3 us; 256 keys and fewer are counted (256: 2 us against 2.6).
+// Replans of 9000 candidates x 2 links x 4 iterations with 512 elites 152.6 ->
+// 135.2 us, with 1000 elites 243.8 -> 153.4 us.
+template <int BS>
+__device__ __forceinline__ void topk_sort_runs(unsigned long long* src, int n, unsigned long long* runs) {
+  const int nr = (n + 63) >> 6;
+  for (int i = static_cast<int>(threadIdx.x); i < 64 * nr; i += BS) {
+    const int r0 = i & ~63;
+    const unsigned long long k = src[min(i, n - 1)];
+    int r = 0;
+#pragma unroll 16
+    for (int q = 0; q < 64; ++q) r += (src[min(r0 + q, n - 1)] < k && r0 + q < n) ? 1 : 0;
+    runs[i < n ? r0 + r : i] = i < n ? k : ~0ull;   // past the end: the last run's tail
+  }
+  __syncthreads();
+  for (int i = static_cast<int>(threadIdx.x); i < n; i += BS) {
+    const unsigned long long k = runs[i];
+    int rank = 0;
+    for (int q0 = 0; q0 < nr; q0 += 8) {
+      int pos[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) pos[u] = 64 * min(q0 + u, nr - 1);
+#pragma unroll
+      for (int step = 32; step > 0; step >>= 1) {
+        unsigned long long c[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) c[u] = runs[pos[u] + step - 1];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) pos[u] += c[u] < k ? step : 0;
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int at = pos[u] - 64 * min(q0 + u, nr - 1) + (runs[pos[u]] < k ? 1 : 0);
+        rank += q0 + u < nr ? at : 0;
+      }
+    }
+    src[rank] = k;
+  }
+}
+
 // Appends key to dst, at slots counted by *counter (one bump per wave), on the
 // lanes where t holds.  Every lane of the wave must call it.
 __device__ __forceinline__ void wave_append(bool t, unsigned long long key, uint32_t* counter,
@@ -1908,17 +1954,28 @@ __device__ __forceinline__ void topk_gather_split(int B, uint32_t lo, Image imag
                                                   uint32_t cap_b) {
   if constexpr (BS >= 1024) {
     // one row at a time, one counter bump per wave and list (measured faster
-    // than the grouped form below in the 1024-thread single-plan kernel)
-    for (int base = 0; base < B; base += BS) {
-      const int b = base + static_cast<int>(threadIdx.x);
-      unsigned long long key = 0ull, hv = 0ull;
-      if (b < B) {
-        const uint32_t im = image(b);
-        key = (static_cast<unsigned long long>(im) << 32) | static_cast<uint32_t>(b);
-        hv = static_cast<unsigned long long>(im - lo) >> shift;
+    // than the grouped form below in the 1024-thread single-plan kernel).  Few
+    // rows of a large batch hold a key of either list: the others cost the wave
+    // one compare (15700 keys: selection 10.2 -> 8.6 us).
+    const unsigned long long end = ((pd + 1ull) << shift) - 1ull;
+    const uint32_t limit = end < 0xFFFFFFFFull ? static_cast<uint32_t>(end) : 0xFFFFFFFFu;
+    constexpr int kRows = 8;   // loaded together
+    for (int base = 0; base < B; base += kRows * BS) {
+      const int b0 = base + static_cast<int>(threadIdx.x);
+      uint32_t v[kRows];
+#pragma unroll
+      for (int u = 0; u < kRows; ++u) v[u] = image(min(b0 + u * BS, B - 1)) - lo;
+#pragma unroll
+      for (int u = 0; u < kRows; ++u) {
+        if (base + u * BS >= B) break;
+        const int b = b0 + u * BS;
+        const bool take = b < B && v[u] <= limit;
+        if (__ballot(take) == 0ull) continue;
+        const unsigned long long key = (static_cast<unsigned long long>(v[u] + lo) << 32) | static_cast<uint32_t>(b);
+        const unsigned long long hv = static_cast<unsigned long long>(v[u]) >> shift;
+        wave_append(take && hv < pd, key, c_lo, d_lo, cap_lo);
+        wave_append(take && hv == pd, key, c_b, d_b, cap_b);
       }
-      wave_append(b < B && hv < pd, key, c_lo, d_lo, cap_lo);
-      wave_append(b < B && hv == pd, key, c_b, d_b, cap_b);
     }
     return;
   }
@@ -1978,11 +2035,12 @@ __device__ __forceinline__ void topk_gather_split(int B, uint32_t lo, Image imag
 // elites, and the rank-th smallest keys (image << 32 | index, all distinct) of
 // the boundary bin complete the set.  A bin that stays larger down to the last
 // digit holds equal images only; a radix over the index bits then orders those
-// ties.  The E keys are finally ordered by counting ranks, or by a bitonic
-// network for very large E.  Batches of at most kTopkBoundary keys rank them without a pass.  (Counting
-// every key against every other, one thread each, was the path of batches up to
-// one key per thread: its compares cost 14 us at 561 keys and 38 us at 1000,
-// this one 7.7 and 7.9 us with the launch of k_set_ctrl in both.)
+// ties.  The E keys are finally ordered by counting ranks, by runs (more than
+// kTopkRunSort) or by a bitonic network (more than kTopkRankSort).  Batches of at
+// most kTopkBoundary keys rank them without a pass.  (Counting every key against
+// every other, one thread each, was the path of batches up to one key per thread:
+// its compares cost 14 us at 561 keys and 38 us at 1000, this one 7.7 and 7.9 us
+// with the launch of k_set_ctrl in both.)
 template <int BS>
 __device__ __forceinline__ const unsigned long long* topk_select(const PlanDesc& P, TopkSmem& sm) {
   const auto cost = gptr(P.cost);
@@ -2093,7 +2151,10 @@ __device__ __forceinline__ const unsigned long long* topk_select(const PlanDesc&
   }
   __syncthreads();
   const unsigned long long* ord;
-  if (E <= kTopkRankSort) {
+  if (E > kTopkRunSort && E <= kTopkRankSort) {
+    topk_sort_runs<BS>(sm.keys, E, sm.sorted);
+    ord = sm.keys;
+  } else if (E <= kTopkRankSort) {
     topk_rank<BS>(sm.keys, E, [&](unsigned long long k, int r) { sm.sorted[r] = k; });
     ord = sm.sorted;
   } else {
