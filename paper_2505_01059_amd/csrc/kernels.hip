@@ -437,7 +437,7 @@ hipError_t launch_iteration_stage(const PlanDesc& P, int stage, int k, int k0, i
       G.gen_k = last ? 0 : k + 1;
       G.gen_spec = last ? 1 : 0;
       const size_t tile = sizeof(float) * static_cast<size_t>(cand_dyn_floats(P.L, P.W, P.T < kTChunk ? P.T : kTChunk));
-      const size_t lds = std::max(tile, kOnePerUnitLds);
+      const size_t lds = seg_lds_bytes(P) > 0 ? tile : std::max(tile, kOnePerUnitLds);
       const hipStream_t gs = side != nullptr ? side->st : st;
       if (side != nullptr) {
         e = hipEventRecord(side->fork, st);

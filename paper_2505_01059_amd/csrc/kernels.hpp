@@ -40,6 +40,10 @@ constexpr int kMinGenBlocks = 32;
 int wide_lanes(const PlanDesc& P);
 int wide_blocks(const PlanDesc& P, int lanes);
 hipError_t launch_rollout_wide(const PlanDesc& P, int lanes, dim3 grid, size_t lds, hipStream_t st, bool one);
+// LDS a time-sliced rollout asks for, so that no two of its workgroups share a
+// compute unit: more than half of the unit's 160 KB, leaving room for a
+// generator workgroup (k_gen_tensor).  From 20 links on the registers see to it.
+inline size_t seg_lds_bytes(const PlanDesc& P) { return P.n_links < 20 ? 84 * 1024 : 0; }
 // Time-sliced pair-lane rollout (rollout_seg.hip): epoch bump, then the
 // persistent launch of P.seg_grid workgroups.
 hipError_t launch_rollout_seg(const PlanDesc& P, hipStream_t st);
@@ -55,6 +59,6 @@ hipError_t seg_configure(PlanDesc* P);
 // keep one workgroup per unit.
 hipError_t gen_configure(PlanDesc* P);
 // defined in plan.cpp
-int segment_count(int groups, int resident_waves);
+int segment_count(int groups, int resident_waves, int T, double step_us);
 
 }  // namespace mtp

@@ -324,16 +324,28 @@ bool mtp::uses_pm_replan(const mtp_config& c) {
          2 * c.horizon * (c.n_gauss - 1) <= kPmNormals && 2 * c.n_layers * c.n_width <= kPmGraph;
 }
 
-// The S in 4..16 whose unit count groups*S is closest above to a whole number
-// of rounds of the resident waves (ties to the smaller S).
-int mtp::segment_count(int groups, int resident_waves) {
-  int best = 4;
-  double best_eff = 0.0;
-  for (int S = 4; S <= 16; ++S) {
-    const long long units = static_cast<long long>(groups) * S;
+// The S in 1..16 with the shortest estimated launch: rounds of units on the
+// resident waves, a unit being T / S steps and a hand-over.  A unit follows its
+// group's previous one, which was taken groups - waves units before the round's
+// own: what that distance does not cover of the hand-over's latency is waited
+// for.  (Step times of one resident wave; us per replan of 4 iterations, S = 2,
+// 4, 8, 16: 1250 groups x 12 links x 64 steps 1082, 1028, 1115, 1483; 1041 x 12 x
+// 128 1774, 1698, 1914, 2519; 1250 x 24 x 64 1735, 1593, 1625, 1764; 2041 x 12 x
+// 64 1419, 1468, 1548, 1992.  2176 x 24 in contact x 256, 6 iterations: 19157,
+// 17288, 16657, 16750.)
+int mtp::segment_count(int groups, int resident_waves, int T, double step_us) {
+  constexpr double kHandOver = 1.0, kLatency = 10.0;   // us
+  const double slack = static_cast<double>(groups) / resident_waves - 1.0;
+  int best = 1;
+  double best_us = 0.0;
+  for (int S = 1; S <= 16 && S <= T; ++S) {
+    const int len = (T + S - 1) / S;
+    const long long units = static_cast<long long>(groups) * ((T + len - 1) / len);
     const long long rounds = (units + resident_waves - 1) / resident_waves;
-    const double eff = static_cast<double>(units) / static_cast<double>(rounds * resident_waves);
-    if (eff > best_eff + 1e-9) { best_eff = eff; best = S; }
+    const double unit = len * step_us;
+    const double wait = S > 1 ? kHandOver + std::max(0.0, kLatency - slack * unit) : 0.0;
+    const double us = static_cast<double>(rounds) * (unit + wait);
+    if (S == 1 || us < best_us) { best_us = us; best = S; }
   }
   return best;
 }

@@ -54,7 +54,7 @@ bool uses_gen_overlap(const mtp_config& c);
 // Whether a single plan's graph-mode replans run as the two kernels of pm_replan.hip.
 bool uses_pm_replan(const mtp_config& c);
 // Segments of the time-sliced rollout for a given number of resident waves.
-int segment_count(int groups, int resident_waves);
+int segment_count(int groups, int resident_waves, int T, double step_us);
 // Rounds of the without-replacement path permutation: 2 L ceil(log2 W).
 int perm_rounds(int L, int W);
 // Time steps per candidate workgroup of the single-plan candidate kernel.
