@@ -14,6 +14,7 @@
 // Per-instance stages run the same tile functions as the single-plan kernels,
 // and every reduction has an order fixed by the instance alone, so a result
 // does not depend on which workgroup ran which tile or on the other instances.
+#define MTP_SHARED_LAUNCH 1   // items read what others of the launch stored
 #include "batch.hpp"
 #include "batch_cand.hpp"
 #include "rollout_wide.hpp"
@@ -38,7 +39,31 @@ struct BatchShared {
   uint32_t pub_pos, pub_count, pub_phase, pub_k;
   int32_t publish;
   int32_t abort;
+  int32_t acquire;  // the item's inputs may be newer than the caches
+  uint32_t fresh;   // positions whose items' inputs are not
 };
+
+// Queue words travel at agent scope, past the XCDs' L2s.
+__device__ __forceinline__ uint32_t load_agent(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+static_assert(sizeof(BatchItem) == 16, "two 64-bit words");
+__device__ __forceinline__ void store_item(BatchItem* p, const BatchItem& it) {
+  uint64_t* w = reinterpret_cast<uint64_t*>(p);
+  store_agent(w, static_cast<uint64_t>(it.phase) << 32 | it.inst);
+  store_agent(w + 1, static_cast<uint64_t>(it.tile) << 32 | it.k);
+}
+
+__device__ __forceinline__ BatchItem load_item(const BatchItem* p) {
+  const uint64_t* w = reinterpret_cast<const uint64_t*>(p);
+  const uint64_t a = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint64_t b = __hip_atomic_load(w + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  BatchItem it;
+  it.inst = static_cast<uint32_t>(a); it.phase = static_cast<uint32_t>(a >> 32);
+  it.k = static_cast<uint32_t>(b); it.tile = static_cast<uint32_t>(b >> 32);
+  return it;
+}
 
 // One rollout tile of each form, out of line (the descriptor is read again from
 // its uniform address).  Inlined into the one persistent kernel, the forms
@@ -86,7 +111,7 @@ __device__ __noinline__ void roll_wide_tile(const PlanDesc* desc, uint32_t tile)
     if constexpr (kPair) total += rollout_half<N, (1 << LG), CONTACT, EQ>(P, b, pos, rep, live);
     else total += rollout_line<N, kLanes, CONTACT>(P, b, pos, rep, live);
   }
-  if (live && pos == kWriter) P.cost[b] = finite_or_inf(P.R == 1 ? total : total / static_cast<float>(P.R));
+  if (live && pos == kWriter) store_result(&P.cost[b], finite_or_inf(P.R == 1 ? total : total / static_cast<float>(P.R)));
 }
 
 template <int N, bool CONTACT>
@@ -160,6 +185,7 @@ __global__ __launch_bounds__(kBatchThreads, MTP_BATCH_MIN_WG_PER_CU) void k_batc
   const int tid = threadIdx.x;
   const uint32_t epoch = ctl->epoch;
   const uint32_t total = ctl->total;
+  if (tid == 0) sh.fresh = 0u;
   // rollout items of several tiles run one tile per pass of this loop: `sub`
   // is the tile of the current item to run next (0: take a new item)
   uint32_t sub = 0;
@@ -174,22 +200,26 @@ __global__ __launch_bounds__(kBatchThreads, MTP_BATCH_MIN_WG_PER_CU) void k_batc
       if (pos >= total) break;
       if (tid == 0) {
         const uint64_t t0 = wall_clock64();
-        while (__hip_atomic_load(&ready[pos], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) != epoch) {
-          if (__hip_atomic_load(&ctl->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u ||
-              wall_clock64() - t0 > wait_ticks) {
+        uint32_t polls = 0u;
+        while (load_agent(&ready[pos]) != epoch) {
+          if ((++polls & 15u) == 0u && (load_agent(&ctl->error) != 0u || wall_clock64() - t0 > wait_ticks)) {
             atomicOr(&ctl->error, 1u);
             sh.abort = 1;
             break;
           }
           __builtin_amdgcn_s_sleep(2);
         }
-        if (!sh.abort) sh.item = queue[pos];
+        if (!sh.abort) sh.item = load_item(&queue[pos]);
+        sh.acquire = pos >= sh.fresh;
+        if (sh.acquire) sh.fresh = load_agent(&ctl->tail);
       }
       __syncthreads();
       if (sh.abort) break;
-      // acquire: the item's inputs were released by the workgroups that made
-      // them (only an invalidation here, no write-back)
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      // Acquire (an invalidation, no write-back).  An item's inputs reached memory
+      // before its position was taken from the tail, so one invalidation serves
+      // every position below the tail read before it: under load most items need
+      // none.
+      if (sh.acquire) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     const uint32_t inst = __builtin_amdgcn_readfirstlane(sh.item.inst);
     const uint32_t phase_word = __builtin_amdgcn_readfirstlane(sh.item.phase);
@@ -246,9 +276,17 @@ __global__ __launch_bounds__(kBatchThreads, MTP_BATCH_MIN_WG_PER_CU) void k_batc
         break;
       }
     }
-    // release the item's results: after the barrier (every wave's stores have
-    // reached the L2) one wave writes the L2 back for the other XCDs, instead
-    // of every wave doing it
+    // Candidate, rollout and refit items store everything at agent scope (another
+    // XCD reads it, or writes it again in the next iteration): waiting for the
+    // stores releases it.  The others' results, and recorded states, take a
+    // write-back of the L2, by one wave after the barrier.  With a write-back
+    // after and an invalidation before every item, and in every poll of the queue,
+    // 32 workgroups kept emptying the L2 they share: uneven instances per launch 4
+    // 4.51 -> 3.82 ms, 8 5.44 -> 4.50, 16 8.17 -> 6.44, 32 10.5 -> 9.9, 256 76.9 ->
+    // 75.0.
+    const bool fenced =
+        phase == kPhShift || phase == kPhPaths || phase == kPhTopk || (phase == kPhRoll && P.n_dbg > 0);
+    stores_done();
     __syncthreads();
     if (phase == kPhRoll) {
       const uint32_t lg = shape_roll_lg(shape);
@@ -261,13 +299,11 @@ __global__ __launch_bounds__(kBatchThreads, MTP_BATCH_MIN_WG_PER_CU) void k_batc
     }
 
     if (tid == 0) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      if (fenced) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       sh.publish = 0;
       const uint32_t nt = phase_tiles(P, phase, shape);
       const uint32_t done = atomicAdd(&ictl[inst].done, 1u) + 1u;
       if (done == nt) {
-        // acquire the other tiles' results (released before their counts)
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         atomicExch(&ictl[inst].done, 0u);
         uint32_t nph, nk;
         if (phase == kPhShift) {
@@ -296,16 +332,14 @@ __global__ __launch_bounds__(kBatchThreads, MTP_BATCH_MIN_WG_PER_CU) void k_batc
         for (uint32_t t = tid; t < m; t += kBatchThreads) {
           BatchItem it;
           it.inst = inst; it.phase = sh.pub_phase | (shape << kItemShapeShift); it.k = sh.pub_k; it.tile = t;
-          queue[p0 + t] = it;
+          store_item(&queue[p0 + t], it);
         }
-        // one release (one L2 write-back) in wave 0, which then sets the ready
-        // flags: the barrier orders every wave's queue entries before it
+        // wave 0 sets the ready flags once every wave's entries have reached memory
+        stores_done();
         __syncthreads();
-        if (tid < 64) {
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        if (tid < 64)
           for (uint32_t t = tid; t < m; t += 64)
             __hip_atomic_store(&ready[p0 + t], epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
       } else if (tid == 0) {
         atomicOr(&ctl->error, 2u);   // queue overflow: items are never published, waiters time out
       }

@@ -35,6 +35,11 @@ struct BatchCandSmem {
 };
 static_assert(kGraphTile >= kMaxLayers * kMaxWidth, "at least one joint's column");
 
+// A control of U, at agent scope (store_agent).
+__device__ __forceinline__ void store_u(__attribute__((address_space(1))) float* p, float v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // The value lane `i` (uniform) of the wave holds.
 __device__ __forceinline__ float lane_value(float v, int i) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
@@ -116,7 +121,7 @@ __device__ __forceinline__ void spline_steps(const PlanDesc& P, const float4 (*t
       for (int i = 0; i < kG; ++i) {
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj)
-          __builtin_nontemporal_store(v[jj][i], (__attribute__((address_space(1))) float*)(out[jj] + off[i]));
+          store_u((__attribute__((address_space(1))) float*)(out[jj] + off[i]), v[jj][i]);
         off[i] += static_cast<uint32_t>(kG * row);
       }
       i0 += kG;
@@ -140,8 +145,7 @@ __device__ __forceinline__ void spline_steps(const PlanDesc& P, const float4 (*t
     for (int q = 0; q < kQ; ++q) w[q] = tb[i0][q];
 #pragma unroll
     for (int jj = 0; jj < NJ; ++jj)
-      __builtin_nontemporal_store(value(w, jj),
-                                  (__attribute__((address_space(1))) float*)(out[jj] + i0 * row) + b);
+      store_u((__attribute__((address_space(1))) float*)(out[jj] + i0 * row) + b, value(w, jj));
   }
 }
 
@@ -249,7 +253,7 @@ __device__ __forceinline__ void batch_cand_tile(const PlanDesc& P, uint32_t r, i
           const size_t at = static_cast<size_t>(l) * P.P + pp;
           const uint32_t wi = P.wor ? static_cast<uint32_t>(Ig[at]) : __umulhi(q.w[c], static_cast<uint32_t>(P.W));
           idx[g] |= wi << (8 * c);
-          if (i_writer) Ig[at] = static_cast<uint8_t>(wi);
+          if (i_writer) store_agent(&P.I[at], static_cast<uint8_t>(wi));
         }
       }
     }
@@ -287,7 +291,7 @@ __device__ __forceinline__ void batch_cand_tile(const PlanDesc& P, uint32_t r, i
                 if (i >= first && i <= last) {
                   const float z = fmaf(span, u01(q.w[c]), lo);
                   sm.z[(i - first) * LW + e] = z;
-                  if (z_writer) Zg[static_cast<size_t>(l) * P.W * P.n + i] = z;
+                  if (z_writer) store_agent(&P.Z[static_cast<size_t>(l) * P.W * P.n + i], z);
                 }
               }
             }
@@ -331,7 +335,7 @@ __device__ __forceinline__ void batch_cand_tile(const PlanDesc& P, uint32_t r, i
               };
               auto put = [&](int t, float z) {
                 const float v = fmaf(lane_value(sg[0], t - t0), z, lane_value(mu[0], t - t0));
-                __builtin_nontemporal_store(__builtin_amdgcn_fmed3f(v, lo, hv), out);
+                store_u(out, __builtin_amdgcn_fmed3f(v, lo, hv));
                 out += row;
               };
               int t4 = t0;
@@ -359,8 +363,8 @@ __device__ __forceinline__ void batch_cand_tile(const PlanDesc& P, uint32_t r, i
         // nominal mean, one step per thread
         for (int j = jg; j < je; ++j)
           for (int t = tc + tid; t < te; t += kCandThreads)
-            __builtin_nontemporal_store(clampf(gptr(P.mu)[t * P.n + j], lo, hi),
-                                        &Ug[(static_cast<size_t>(t) * P.n + j) * ld + tens_hi]);
+            store_u(&Ug[(static_cast<size_t>(t) * P.n + j) * ld + tens_hi],
+                    clampf(gptr(P.mu)[t * P.n + j], lo, hi));
       }
     }
   }

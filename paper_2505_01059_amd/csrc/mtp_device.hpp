@@ -135,6 +135,31 @@ __device__ __forceinline__ __attribute__((address_space(1))) T* gptr(T* p) {
   return (__attribute__((address_space(1))) T*)(p);
 }
 
+// Stores at agent scope go past the XCD's L2: once the wave has waited for them
+// (stores_done), every XCD reads the values without a write-back of the L2.
+template <class T>
+__device__ __forceinline__ void store_agent(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Costs, moments and action: at agent scope where they are read or written again
+// by other compute units within the launch (the batched launch, which sets
+// MTP_SHARED_LAUNCH), else plain stores, which end sooner (561 candidates x 3 links: 163.2 us per replan, 166.8 at agent scope).
+#ifndef MTP_SHARED_LAUNCH
+#define MTP_SHARED_LAUNCH 0
+#endif
+__device__ __forceinline__ void store_result(float* p, float v) {
+  if constexpr (MTP_SHARED_LAUNCH) store_agent(p, v);
+  else *gptr(p) = v;
+}
+
+// Waits until this wave's stores have reached memory.
+__device__ __forceinline__ void stores_done() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vector memory
+  asm volatile("" ::: "memory");
+}
+
 constexpr uint32_t kTagZ = 1, kTagI = 2, kTagEps = 3, kTagPerm = 4;
 
 __device__ __forceinline__ uint32_t stream_c3(uint32_t tag, int k) {
@@ -684,7 +709,7 @@ __device__ __forceinline__ void rollout_point_mass(const PlanDesc& P, int b, con
   };
   if (__builtin_amdgcn_ballot_w64(b < P.n_dbg) != 0) run(std::true_type{});
   else run(std::false_type{});
-  P.cost[b] = finite_or_inf(cost);
+  store_result(&P.cost[b], finite_or_inf(cost));
 }
 
 // Obstacle-table size class of a point-mass plan: 8, 16, 24, 32 in registers, 0 in LDS.
@@ -965,7 +990,7 @@ __device__ __forceinline__ void rollout_chain(const PlanDesc& P, int b) {
   }
   total += cost;
   }
-  P.cost[b] = finite_or_inf(R == 1 ? total : total / static_cast<float>(R));
+  store_result(&P.cost[b], finite_or_inf(R == 1 ? total : total / static_cast<float>(R)));
 }
 
 // ------------------------------------------------------------------ quad-lane chain
@@ -1185,7 +1210,7 @@ __device__ __forceinline__ void rollout_chain_quad(const PlanDesc& P, int b, int
   if (__builtin_amdgcn_ballot_w64(b < P.n_dbg) != 0) run(std::true_type{});
   else run(std::false_type{});
   cost = fmaf(wu, quad_sum(uacc), cost);
-  if (s == 0) P.cost[b] = finite_or_inf(cost);
+  if (s == 0) store_result(&P.cost[b], finite_or_inf(cost));
 }
 
 // ------------------------------------------------------------------ pair-lane chain
@@ -1591,7 +1616,7 @@ __device__ __forceinline__ void rollout_chain_pair(const PlanDesc& P, int b, boo
     pair_steps<N, CONTACT>(P, K, b, ph, om, turn, cost, 0, P.T, true, rep);
     total += cost;
   }
-  if (!B) P.cost[b] = finite_or_inf(R == 1 ? total : total / static_cast<float>(R));
+  if (!B) store_result(&P.cost[b], finite_or_inf(R == 1 ? total : total / static_cast<float>(R)));
 }
 
 // ------------------------------------------------------------------ time-sliced pair rollout
@@ -1701,13 +1726,10 @@ __device__ __forceinline__ void rollout_pair_segmented(const PlanDesc& P, SegCtl
         if (rec) put(2 * M + 1 + i, turn[i]);
       }
       put(2 * M, cost);
-      // every lane's state has reached memory before the flag does
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_waitcnt(0x0F70);   // vector memory
-      asm volatile("" ::: "memory");
+      stores_done();   // every lane's state, before the flag
       if (lane == 0) __hip_atomic_store(&done[g], seg_tag(epoch, seg + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else if (live && !B) {
-      P.cost[b] = finite_or_inf(cost);
+      store_result(&P.cost[b], finite_or_inf(cost));
     }
   }
 }
@@ -2434,10 +2456,10 @@ __device__ __forceinline__ void update_output_from(const PlanDesc& P, int o, Wei
   if (mu_new) *mu_new = mn;
   if (sg_new) *sg_new = sn;
   if (lane == 0) {
-    mu[o] = mn;
-    sigma[o] = sn;
+    store_result(&P.mu[o], mn);
+    store_result(&P.sigma[o], sn);
     // first control of the best candidate (lane 0 holds elite 0 already)
-    if (o < P.n) gptr(P.action)[o] = P.E <= 64 * kUpdKeep ? keep[0] : val(0);
+    if (o < P.n) store_result(&P.action[o], P.E <= 64 * kUpdKeep ? keep[0] : val(0));
   }
 }
 
