@@ -10,17 +10,31 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmtp.so")
 
-SOURCES = ["kernels.hip", "rollout_quad.hip", "rollout_seg.hip", "rollout_wide.hip", "pm_replan.hip", "plan.cpp", "batch.hip", "batch.cpp", "server.cpp", "plant.cpp", "noalloc.hip",
-           "schedule_cache.cpp"]
-# The batched persistent kernel, the quad-lane and the time-sliced pair-lane
-# rollouts run one wave per SIMD, and LLVM's iterative ILP scheduler orders their
-# long dependent chains better than the default (measured: 256-instance batched
-# replan 86.1 -> 82.2 ms; 24-link contact rollout 3756 -> 3640 us).
+SOURCES = ["kernels.hip", "rollout_line.hip", "rollout_quad.hip", "rollout_seg.hip", "rollout_wide.hip",
+           "rollout_wide_half.hip", "rollout_wide_rest.hip", "pm_replan.hip", "plan.cpp", "batch.hip", "batch.cpp",
+           "server.cpp", "plant.cpp", "noalloc.hip", "schedule_cache.cpp"]
+
+
+def _sched(strategy):
+    return ["-mllvm", f"-amdgpu-sched-strategy={strategy}"]
+
+
+# Most kernels run one wave per SIMD, so the instruction order decides how much of
+# a wave's latency shows, and each form has an order that suits it.  Launches in us
+# with LLVM's default / iterative-ilp / max-ilp scheduler (values are the same):
+# time-sliced 24 links in contact 2910 / 2945 / 2900; one lane, 4 links, 40000
+# candidates 80 / 76 / 76; four lanes, 12 links 89 / 92 / 86; eight lanes, 24 links
+# 121 / 122 / 115; four lanes, 24 links in contact 748 / 760 / 762; four lanes, 7
+# links in contact, three models 168 / 161 / 168; four lanes, 4 links 55.6 / 58.0 /
+# 55.9; quad lanes, 7 links 109.5 / 110.8 / 110.6.  Whole point-mass replans 75.8 /
+# 74.4 / 74.8 us; 256 instances batched 77.1 / 76.7 / 76.9 ms.
 EXTRA_FLAGS = {
-    "batch.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
-    "rollout_quad.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
-    "rollout_wide.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
-    "rollout_seg.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
+    "batch.hip": _sched("iterative-ilp"),
+    "pm_replan.hip": _sched("iterative-ilp"),
+    "rollout_line.hip": _sched("iterative-ilp"),
+    "rollout_seg.hip": _sched("max-ilp"),
+    "rollout_wide.hip": _sched("iterative-ilp"),
+    "rollout_wide_half.hip": _sched("max-ilp"),
 }
 HIP_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

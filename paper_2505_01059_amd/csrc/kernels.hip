@@ -89,13 +89,6 @@ __global__ __launch_bounds__(kRollThreads) void k_rollout_point_mass(PlanDesc P)
 }
 
 template <int N, bool CONTACT, bool ONE>
-__global__ __launch_bounds__(kRollThreads) MTP_ROLL_WAVES(ONE) void k_rollout_chain(PlanDesc P) {
-  if (static_cast<int>(blockIdx.x) >= P.roll_blocks) { gen_tensor_tiles(P); return; }
-  const int b = xcd_contiguous_block(blockIdx.x, P.roll_blocks) * kRollThreads + threadIdx.x;
-  if (b < P.B) rollout_chain<N, CONTACT>(P, b);
-}
-
-template <int N, bool CONTACT, bool ONE>
 __global__ __launch_bounds__(kRollThreads) MTP_ROLL_WAVES(ONE || N >= 20) void k_rollout_chain_pair(PlanDesc P) {
   if (static_cast<int>(blockIdx.x) >= P.roll_blocks) { gen_tensor_tiles(P); return; }
   const int g = xcd_contiguous_block(blockIdx.x, P.roll_blocks) * kRollThreads + threadIdx.x;
@@ -326,15 +319,7 @@ static hipError_t launch_rollout_kernel(const PlanDesc& P, dim3 grid, size_t lds
     }
     return hipErrorInvalidValue;
   }
-  if (P.dyn == kChain) {
-    switch (P.n_links) {
-#define X(N) case N: if constexpr (!pair_chain_links<N>() && !quad_chain_links<N>()) { k_rollout_chain<N, false, ONE><<<grid, kRollThreads, lds, st>>>(P); return hipGetLastError(); } break;
-      MTP_CHAIN_LINKS(X)
-#undef X
-      default: break;
-    }
-    return hipErrorInvalidValue;
-  }
+  if (P.dyn == kChain) return launch_rollout_line(P, grid, lds, st, ONE);
   switch (P.n_links) {
 #define X(N) case N: if constexpr (!pair_chain_links<N>()) { k_rollout_chain<N, true, ONE><<<grid, kRollThreads, lds, st>>>(P); return hipGetLastError(); } break;
     MTP_CONTACT_LINKS(X)

@@ -46,4 +46,12 @@ __device__ __forceinline__ void gen_tensor_tiles(const PlanDesc& P) {
 // in flight); otherwise the usual occupancy target.
 #define MTP_ROLL_WAVES(one) __attribute__((amdgpu_waves_per_eu(1, (one) ? 1 : 8)))
 
+// One candidate per lane: the chains too short for the other narrow forms.
+template <int N, bool CONTACT, bool ONE>
+__global__ __launch_bounds__(kRollThreads) MTP_ROLL_WAVES(ONE) void k_rollout_chain(PlanDesc P) {
+  if (static_cast<int>(blockIdx.x) >= P.roll_blocks) { gen_tensor_tiles(P); return; }
+  const int b = xcd_contiguous_block(blockIdx.x, P.roll_blocks) * kRollThreads + threadIdx.x;
+  if (b < P.B) rollout_chain<N, CONTACT>(P, b);
+}
+
 }  // namespace mtp

@@ -1,8 +1,6 @@
 // Time-sliced pair-lane rollout kernels (long chains whose pair-lane waves
-// outnumber the SIMDs) and their launcher.  A unit of its own: these kernels
-// run one wave per SIMD with long dependent chains in every lane, and LLVM's
-// iterative ILP machine scheduler hides more of their latency than the default
-// (24-link contact chain: 3756 -> 3640 us per launch).
+// outnumber the SIMDs) and their launcher.  A unit of its own so that it can be
+// compiled with its own scheduling options.
 #include <algorithm>
 
 #include "kernels.hpp"
