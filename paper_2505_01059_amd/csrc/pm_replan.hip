@@ -16,8 +16,8 @@
 // candidates x 50 steps, of about 9 us: controls 1.1, states 0.9, cost terms 1.9
 // (the one phase bound by issue: 20 obstacle tests for each of 1600 points on
 // one compute unit), their sums 0.6, selection 2.7, refit 1.9.  Replans before
-// -> now: 288 x 50 x 10 iterations 0.187 -> 0.098 ms; 256 x 20 x 10
-// 0.171 -> 0.076 ms.
+// -> now: 288 x 50 x 10 iterations 0.187 -> 0.096 ms; 256 x 20 x 10
+// 0.171 -> 0.075 ms.
 #include <algorithm>
 
 #include "kernels.hpp"

@@ -16,7 +16,7 @@ int wide_blocks(const PlanDesc& P, int lanes) {
 // takes one wave's time whatever its size, which more lanes shorten; a second
 // wave on a SIMD costs more than the lanes save, because the solver's row
 // passes issue for every lane (64 steps, us per launch: 24 links, 4000
-// candidates 222 -> 150 on four lanes -> 126 on eight; 14500 candidates 222
+// candidates 222 -> 150 on four lanes -> 115 on eight; 14500 candidates 222
 // against 264 on eight lanes, 1812 waves).  Plain chains of two and three
 // links stay narrow: moving three rows across lanes costs what it saves
 // (3 links, 561 candidates: 30.6 us narrow, 33.0 on four lanes).  Randomised
