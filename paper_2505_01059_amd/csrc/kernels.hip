@@ -5,6 +5,7 @@
 #include "kernels.hpp"
 #include "pm_tile.hpp"
 #include "rollout_grid.hpp"
+#include "wave_select.hpp"
 
 namespace mtp {
 
@@ -179,10 +180,9 @@ __global__ __launch_bounds__(kUpdThreads) void k_refit_regen(PlanDesc P, int k, 
 // same values in each; the first stores them), then four of its waves refit one
 // step each, as k_update, or k_update_next with NEXT.  The selection is one
 // workgroup's latency either way, and one launch less is a microsecond per
-// iteration.  Replans in two launches -> one: 561 candidates x 3 links x 4
-// iterations 165.0 -> 162.1 us; 9216 x 7 x 8 1.020 -> 1.002 ms; 3376 x 12 x 6
-// 0.631 -> 0.621 ms; 3341 point masses x 6 153.3 -> 146.2 us; 13500 x 4 x 4 0.310
-// -> 0.303 ms.
+// iteration.  Replans in two launches -> one (candidates x links x iterations):
+// 9216 x 7 x 8 1.020 -> 1.002 ms; 3376 x 12 x 6 0.631 -> 0.621 ms; 3341 point
+// masses x 6 153.3 -> 146.2 us; 13500 x 4 x 4 0.310 -> 0.303 ms.
 constexpr int kFusedThreads = kTopkThreads;
 template <bool NEXT>
 __global__ __launch_bounds__(kFusedThreads) void k_select_refit(PlanDesc P, int k_next) {
@@ -211,6 +211,62 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_refit(PlanDesc P, int 
   if constexpr (NEXT) {
     __syncthreads();
     local_store<kFusedThreads>(P, P.U2, tq, j, k_next, r, z, mom);
+  }
+}
+
+// The same for few candidates and elites: one wave selects without barriers while
+// the others draw their normals, in a workgroup of a refit tile's size.
+constexpr int kSelectWave = kUpdThreads / 64 - 1;   // the wave with the fewest local samples to draw
+template <bool NEXT>
+__global__ __launch_bounds__(kUpdThreads) void k_select_refit_wave(PlanDesc P, int k_next) {
+  __shared__ WaveSelectSmem sm;
+  __shared__ int elite[64];
+  __shared__ float weight[64];
+  __shared__ float mom[4][2];
+  const int tq = static_cast<int>(blockIdx.x) / P.n, j = static_cast<int>(blockIdx.x) - tq * P.n;
+  const int c = static_cast<int>(threadIdx.x) >> 6, lane = threadIdx.x & 63;
+  const int t = 4 * tq + c;
+  const uint32_t r = P.ctrl[0];
+  if (c == kSelectWave) {
+    const auto cost = gptr(P.cost);
+    float v[kWaveKeys];
+    uint32_t o[kWaveKeys];
+#pragma unroll
+    for (int q = 0; q < kWaveKeys; ++q) v[q] = cost[min(lane + 64 * q, P.B - 1)];
+#pragma unroll
+    for (int q = 0; q < kWaveKeys; ++q) o[q] = lane + 64 * q < P.B ? cost_order(v[q]) : 0xFFFFFFFFu;
+    // as topk_block: the values that an image does not give back are read again
+    const WaveElite el = wave_elites(o, lane, P.B, P.E, P.lam, sm, [&](int idx, float v) {
+      return (v == 0.0f || v == INFINITY) ? cost[idx] : v;
+    });
+    if (lane < P.E) {
+      elite[lane] = el.idx;
+      weight[lane] = el.weight;
+      if (blockIdx.x == 0) {
+        gptr(P.eidx)[lane] = el.idx;
+        gptr(P.ecost)[lane] = el.cost;
+        gptr(P.w)[lane] = el.weight;
+        if (lane == 0 && !(el.best < INFINITY)) atomicOr(&P.ctrl[2], 1u);
+      }
+    }
+  }
+  float z[kLocalKeep][4];
+  if constexpr (NEXT) local_normals<kUpdThreads>(P, tq, j, k_next, r, z);
+  if (P.gen_spec && blockIdx.x == 0 && threadIdx.x == 0) {   // as k_update
+    P.ctrl[3] = P.ctrl[0] + 1u;
+    P.ctrl[5] = 1u;
+  }
+  __syncthreads();
+  if (t < P.T) {
+    const int o = t * P.n + j;
+    const auto row = gptr(P.U) + static_cast<size_t>(o) * static_cast<size_t>(P.ldU);
+    float mn, sn;
+    update_output_from(P, o, weight, [&](int e) { return row[elite[e]]; }, &mn, &sn);
+    if (lane == 0) { mom[c][0] = mn; mom[c][1] = sn; }
+  }
+  if constexpr (NEXT) {
+    __syncthreads();
+    local_store<kUpdThreads>(P, P.U2, tq, j, k_next, r, z, mom);
   }
 }
 
@@ -468,8 +524,17 @@ static bool fuses_refit(const PlanDesc& P) {
          !refit_regenerates(P.interp, P.p, P.wor, P.E, P.B);
 }
 
+// By one wave where it holds every cost in its registers and an elite per lane,
+// on up to four of its small workgroups per compute unit.  Replans on the
+// 1024-thread selection (or its two launches) -> by one wave: 561 candidates x 3
+// links x 4 iterations 162.3 -> 152.6 us; 780 point masses x 6 140.4 -> 124.4 us;
+// 900 x 7 x 6 422 -> 406 us; 900 x 12 x 128 steps x 6 (384 tiles) 1057 -> 1034 us.
+static bool selects_by_wave(const PlanDesc& P) {
+  return (P.diag & 1) == 0 && P.B <= 64 * kWaveKeys && P.E <= 64 && ((P.T + 3) / 4) * P.n <= 4 * P.gen_grid;
+}
+
 hipError_t launch_iteration(const PlanDesc& P, int k, int k0, int k1, hipStream_t st, const SideLane* side) {
-  const bool fused = fuses_refit(P);
+  const bool by_wave = selects_by_wave(P), fused = by_wave || fuses_refit(P);
   for (int stage = 0; stage < (fused ? 2 : 4); ++stage) {
     const hipError_t e = launch_iteration_stage(P, stage, k, k0, k1, st, side);
     if (e != hipSuccess) return e;
@@ -480,8 +545,14 @@ hipError_t launch_iteration(const PlanDesc& P, int k, int k0, int k1, hipStream_
   if (ahead && ((k1 - 1 - k) & 1)) { Pk.U = P.U2; Pk.U2 = P.U; }
   Pk.gen_spec = (ahead && last && P.spec && k0 == 0 && k1 == P.K) ? 1 : 0;
   const int tiles = ((P.T + 3) / 4) * P.n;
-  if (ahead && !last) k_select_refit<true><<<tiles, kFusedThreads, 0, st>>>(Pk, k + 1);
-  else k_select_refit<false><<<tiles, kFusedThreads, 0, st>>>(Pk, -1);
+  if (by_wave) {
+    if (ahead && !last) k_select_refit_wave<true><<<tiles, kUpdThreads, 0, st>>>(Pk, k + 1);
+    else k_select_refit_wave<false><<<tiles, kUpdThreads, 0, st>>>(Pk, -1);
+  } else if (ahead && !last) {
+    k_select_refit<true><<<tiles, kFusedThreads, 0, st>>>(Pk, k + 1);
+  } else {
+    k_select_refit<false><<<tiles, kFusedThreads, 0, st>>>(Pk, -1);
+  }
   return hipGetLastError();
 }
 
