@@ -317,7 +317,8 @@ mtp_status mtp_batch_set_state(mtp_batch* b, int32_t i, const float* d_mu, const
  *                  0 = never, 100 = fewer tiles than workgroups.  Unless 0, an
  *                  instance whose own stages take longer in turn than most of the
  *                  launch's work per workgroup also runs the finest items, with
- *                  more lanes per candidate in its rollout
+ *                  more lanes per candidate in its rollout, where the estimates of
+ *                  mtp_batch_item_shapes say that this is shorter
  * Defaults: {0, 1, 1, 1, 64, 100}.
  */
 typedef struct {
@@ -373,6 +374,20 @@ mtp_status mtp_schedule_cache_lookup(const char* path, const char* arch, int32_t
                                      mtp_batch_schedule* h_out, float* h_ms, int32_t* h_found);
 mtp_status mtp_schedule_cache_store(const char* path, const char* arch, int32_t cus, uint64_t mix,
                                     const mtp_batch_schedule* h_schedule, float ms);
+/* Scheduling of the batched launch: the items a launch of all these instances on
+ * `workgroups` persistent workgroups is cut into under a schedule, and the
+ * estimates they are chosen by (one CEM iteration of the instance, chosen items
+ * and the launch's plain ones).  Host only; h_out receives n entries. */
+typedef struct {
+  int32_t finest;         /* the finest items (see split_pct), else the schedule's */
+  int32_t wide_lg;        /* log2 of the rollout's lanes per candidate over the narrow form */
+  double path_us;         /* the instance's stages in turn, with every workgroup its own */
+  double plain_path_us;
+  double work_us;         /* its work in all, per workgroup */
+  double plain_work_us;
+} mtp_batch_items;
+mtp_status mtp_batch_item_shapes(const mtp_config* cfgs, int32_t n, int32_t workgroups,
+                                 const mtp_batch_schedule* h_schedule, mtp_batch_items* h_out);
 /* As mtp_set_graph_mode, for the persistent launch. */
 mtp_status mtp_batch_set_graph_mode(mtp_batch* b, int32_t use_graph);
 /* Release the batch object (the workspace stays the caller's). */

@@ -90,6 +90,84 @@ uint32_t coarse_shape(const mtp_batch_schedule& s) {
   return make_shape(log2_of(s.cand_tiles), 0u, log2_of(s.roll_tiles), log2_of(s.refit_outputs));
 }
 
+// One instance's part in a launch: its config and how many iterations it runs.
+struct LaunchPart {
+  const mtp_config* cfg;
+  int iters;
+};
+
+// Item shapes of the instances of a launch on `workgroups` persistent workgroups
+// under schedule s, and in *plain the shape of the launch as a whole.
+std::vector<uint32_t> choose_shapes(const std::vector<LaunchPart>& parts, int workgroups, const mtp_batch_schedule& s,
+                                    uint32_t* plain) {
+  // Few active instances leave most workgroups idle while their candidate
+  // tiles run, each tile covering all joints one after another, and while
+  // their refit items run many outputs each: then every (tile, joint) and
+  // every four outputs become items of their own.  With many instances the
+  // items stay large (far fewer of them through the one queue counter).
+  uint64_t cand_tiles = 0;
+  for (const LaunchPart& p : parts)
+    cand_tiles += static_cast<uint64_t>((p.cfg->n_tensor + p.cfg->n_gauss + kCandThreads - 1) / kCandThreads);
+  const bool light = cand_tiles * 100u < static_cast<uint64_t>(s.split_pct) * static_cast<uint64_t>(workgroups);
+  const uint32_t shape = light ? kShapeFinest : coarse_shape(s);
+  *plain = shape;
+  std::vector<uint32_t> shapes(parts.size(), shape);
+  if (s.split_pct <= 0) return shapes;
+  // The launch cannot end before its longest instance, whose stages run one
+  // after another: an instance whose own path is more than kPathShare of the
+  // launch's work per workgroup takes finer items, then wide rollout tiles
+  // (shorter while the narrow ones leave workgroups idle, at more work in
+  // total), the first that are short enough.  0.7 measured best of 0.5, 0.7 and 1
+  // over 8 to 32 uneven instances (the queue makes every instance wait its turn,
+  // so a path as long as the whole work is already too long); launches with more
+  // work keep the plain shape.
+  constexpr double kPathShare = 0.7;
+  auto cost = [&](size_t a, uint32_t sh) {
+    StageCost c = stage_cost(*parts[a].cfg, sh, workgroups);
+    c.path *= parts[a].iters;
+    c.work *= parts[a].iters;
+    return c;
+  };
+  auto rung = [](uint32_t lg) { return kShapeFinest | make_shape(0, 0, 0, 0, lg); };
+  double work = 0.0;
+  for (size_t a = 0; a < parts.size(); ++a) work += cost(a, shape).work;
+  const double limit = kPathShare * work / workgroups;
+  std::vector<size_t> longer;   // instances that no shape brings under the limit
+  for (size_t a = 0; a < parts.size(); ++a) {
+    if (cost(a, shape).path <= limit) continue;
+    const uint32_t widest = max_wide_lg(parts[a].cfg->dynamics, parts[a].cfg->n_links);
+    bool under = false;
+    for (uint32_t lg = 0; lg <= widest && !under; ++lg)
+      if (cost(a, rung(lg)).path <= limit) {
+        shapes[a] = rung(lg);
+        under = true;
+      }
+    if (!under) longer.push_back(a);
+  }
+  // Those set the launch's time: each takes the shape with the shortest path
+  // together with the work it puts in the way of the others, and none whose path
+  // is longer than the plain shape's.  Once the workgroups have a tile each, more
+  // lanes only add rounds (ms for two iterations, one lane group, twice, four
+  // times the lanes: 8704 candidates x 24 links in contact x 256 steps alone 3.27,
+  // 2.12, 2.98; 69632 alone 10.2, 9.9, 13.2, two of them 15.7, 16.9, 24.2; four of
+  // 4000 x 24 x 128 without contact 1.48, 1.15, 1.46).
+  for (const size_t a : longer) {
+    const double others = static_cast<double>(longer.size() - 1) / workgroups;
+    const StageCost base = cost(a, shape);
+    double best = base.path + others * base.work;
+    const uint32_t widest = max_wide_lg(parts[a].cfg->dynamics, parts[a].cfg->n_links);
+    for (uint32_t lg = 0; lg <= widest; ++lg) {
+      const StageCost c = cost(a, rung(lg));
+      const double t = c.path + others * c.work;
+      if (c.path <= base.path && t < best) {
+        best = t;
+        shapes[a] = rung(lg);
+      }
+    }
+  }
+  return shapes;
+}
+
 struct BatchLayout {
   size_t ctl, descs, ictl, order, out, queue, ready, inst0;
   std::vector<size_t> res, tr;
@@ -600,40 +678,10 @@ mtp_status mtp_batch_step(mtp_batch* b, int32_t n_active, const int32_t* h_activ
     c.x0_off = (d_x0_packed != nullptr && kb == 0) ? x0_offsets[i] : -1;
     b->h_order[a] = i;
   }
-  // Few active instances leave most workgroups idle while their candidate
-  // tiles run, each tile covering all joints one after another, and while
-  // their refit items run many outputs each: then every (tile, joint) and
-  // every four outputs become items of their own.  With many instances the
-  // items stay large (far fewer of them through the one queue counter).
-  uint64_t cand_tiles = 0;
-  for (int a = 0; a < n_active; ++a) {
-    const mtp_config& c = b->cfgs[h_active[a]];
-    cand_tiles += static_cast<uint64_t>((c.n_tensor + c.n_gauss + kCandThreads - 1) / kCandThreads);
-  }
-  const bool light = cand_tiles * 100u < static_cast<uint64_t>(b->sched.split_pct) * static_cast<uint64_t>(b->grid);
-  const uint32_t shape = light ? kShapeFinest : coarse_shape(b->sched);
-  // The launch cannot end before its longest instance, whose stages run one
-  // after another: an instance whose own path is more than kPathShare of the
-  // launch's work per workgroup takes finer items, then wide rollout tiles
-  // (shorter, at more work in total), until it is not.  0.7 measured best of
-  // 0.5, 0.7 and 1 over 8 to 32 uneven instances (the queue makes every
-  // instance wait its turn, so a path as long as the whole work is already
-  // too long); launches with more work keep the plain shape.
-  constexpr double kPathShare = 0.7;
-  std::vector<uint32_t> shapes(n_active, shape);
-  if (b->sched.split_pct > 0) {
-    double work = 0.0;
-    for (int a = 0; a < n_active; ++a)
-      work += (h_k_end[a] - h_k_begin[a]) * stage_cost(b->cfgs[h_active[a]], shape, b->grid).work;
-    const double limit = kPathShare * work / b->grid;
-    for (int a = 0; a < n_active; ++a) {
-      const mtp_config& c = b->cfgs[h_active[a]];
-      const int iters = h_k_end[a] - h_k_begin[a];
-      const uint32_t widest = max_wide_lg(c.dynamics, c.n_links);
-      for (uint32_t lg = 0; lg <= widest && iters * stage_cost(c, shapes[a], b->grid).path > limit; ++lg)
-        shapes[a] = kShapeFinest | make_shape(0, 0, 0, 0, lg);
-    }
-  }
+  std::vector<LaunchPart> parts(n_active);
+  for (int a = 0; a < n_active; ++a) parts[a] = {&b->cfgs[h_active[a]], h_k_end[a] - h_k_begin[a]};
+  uint32_t shape = 0;
+  std::vector<uint32_t> shapes = choose_shapes(parts, b->grid, b->sched, &shape);
   auto count = [&]() {
     uint64_t sum = 0;
     for (int a = 0; a < n_active; ++a) sum += items_for(b->cfgs[h_active[a]], h_k_begin[a], h_k_end[a], shapes[a]);
@@ -729,6 +777,30 @@ mtp_status mtp_batch_set_schedule_full(mtp_batch* b, const mtp_batch_schedule* h
 mtp_status mtp_batch_get_schedule(const mtp_batch* b, mtp_batch_schedule* h_schedule) {
   if (b == nullptr || h_schedule == nullptr) return MTP_ERR_INVALID_ARG;
   *h_schedule = b->sched;
+  return MTP_OK;
+}
+
+mtp_status mtp_batch_item_shapes(const mtp_config* cfgs, int32_t n, int32_t workgroups,
+                                 const mtp_batch_schedule* h_schedule, mtp_batch_items* h_out) {
+  if (cfgs == nullptr || n < 1 || workgroups < 1 || h_schedule == nullptr || h_out == nullptr ||
+      !schedule_valid(*h_schedule))
+    return MTP_ERR_INVALID_ARG;
+  std::vector<LaunchPart> parts(n);
+  for (int32_t i = 0; i < n; ++i) {
+    mtp_status code = MTP_OK;
+    if (!validate_config(&cfgs[i], nullptr, &code)) return code;
+    parts[i] = {&cfgs[i], cfgs[i].n_iters};
+  }
+  uint32_t plain = 0;
+  const std::vector<uint32_t> shapes = choose_shapes(parts, workgroups, *h_schedule, &plain);
+  for (int32_t i = 0; i < n; ++i) {
+    h_out[i].finest = (shapes[i] & ~make_shape(0, 0, 0, 0, 3)) == kShapeFinest ? 1 : 0;
+    h_out[i].wide_lg = static_cast<int32_t>(shape_wide_lg(shapes[i]));
+    h_out[i].path_us = stage_cost(cfgs[i], shapes[i], workgroups).path;
+    h_out[i].plain_path_us = stage_cost(cfgs[i], plain, workgroups).path;
+    h_out[i].work_us = stage_cost(cfgs[i], shapes[i], workgroups).work / workgroups;
+    h_out[i].plain_work_us = stage_cost(cfgs[i], plain, workgroups).work / workgroups;
+  }
   return MTP_OK;
 }
 
