@@ -35,9 +35,14 @@ hipError_t launch_rollout_quad(const PlanDesc& P, dim3 grid, size_t lds, hipStre
 constexpr int kPmOverlapLanes = 8;
 // Workgroups that a drawing-ahead rollout launch adds at least.
 constexpr int kMinGenBlocks = 32;
+// Estimated time (us) of a wave of a chain's narrow form through the horizon, one
+// wave per SIMD, and of `gens` generator workgroups.
+double narrow_wave_us(const PlanDesc& P);
+double gen_us(const PlanDesc& P, int gens);
 // Wide rollout forms (rollout_wide.hip): the lanes per candidate a plan's
-// launch takes (0: its narrow form), the workgroups and the launch itself.
-int wide_lanes(const PlanDesc& P);
+// launch takes (0: its narrow form; gen: the launch also draws ahead), the
+// workgroups and the launch itself.
+int wide_lanes(const PlanDesc& P, bool gen);
 int wide_blocks(const PlanDesc& P, int lanes);
 hipError_t launch_rollout_wide(const PlanDesc& P, int lanes, dim3 grid, size_t lds, hipStream_t st, bool one);
 hipError_t launch_wide_half(const PlanDesc& P, int lanes, dim3 grid, size_t lds, hipStream_t st, bool one);
