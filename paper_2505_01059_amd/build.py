@@ -10,9 +10,9 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmtp.so")
 
-SOURCES = ["kernels.hip", "rollout_line.hip", "rollout_quad.hip", "rollout_seg.hip", "rollout_wide.hip",
-           "rollout_wide_half.hip", "rollout_wide_rest.hip", "pm_replan.hip", "plan.cpp", "batch.hip", "batch.cpp",
-           "server.cpp", "plant.cpp", "noalloc.hip", "schedule_cache.cpp"]
+SOURCES = ["kernels.hip", "rollout_line.hip", "rollout_quad.hip", "rollout_quad_gen.hip", "rollout_seg.hip",
+           "rollout_wide.hip", "rollout_wide_half.hip", "rollout_wide_rest.hip", "pm_replan.hip", "plan.cpp",
+           "batch.hip", "batch.cpp", "server.cpp", "plant.cpp", "noalloc.hip", "schedule_cache.cpp"]
 
 
 def _sched(strategy):
@@ -26,12 +26,14 @@ def _sched(strategy):
 # candidates 80 / 76 / 76; four lanes, 12 links 89 / 92 / 86; eight lanes, 24 links
 # 121 / 122 / 115; four lanes, 24 links in contact 748 / 760 / 762; four lanes, 7
 # links in contact, three models 168 / 161 / 168; four lanes, 4 links 55.6 / 58.0 /
-# 55.9; quad lanes, 7 links 109.5 / 110.8 / 110.6.  Whole point-mass replans 75.8 /
+# 55.9; quad lanes, 7 links 109.5 / 110.8 / 110.6, but as long as their generator
+# 200 / 145 / 200 (14000 candidates, a unit of its own).  Whole point-mass replans 75.8 /
 # 74.4 / 74.8 us; 256 instances batched 77.1 / 76.7 / 76.9 ms.
 EXTRA_FLAGS = {
     "batch.hip": _sched("iterative-ilp"),
     "pm_replan.hip": _sched("iterative-ilp"),
     "rollout_line.hip": _sched("iterative-ilp"),
+    "rollout_quad_gen.hip": _sched("iterative-ilp"),
     "rollout_seg.hip": _sched("max-ilp"),
     "rollout_wide.hip": _sched("iterative-ilp"),
     "rollout_wide_half.hip": _sched("max-ilp"),

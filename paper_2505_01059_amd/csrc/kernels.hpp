@@ -31,6 +31,7 @@ hipError_t launch_iteration(const PlanDesc& P, int k, int k0, int k1, hipStream_
 // Quad-lane chain rollout (rollout_quad.hip); one: the launch holds one
 // workgroup per compute unit.
 hipError_t launch_rollout_quad(const PlanDesc& P, dim3 grid, size_t lds, hipStream_t st, bool one);
+hipError_t launch_rollout_quad_gen(const PlanDesc& P, dim3 grid, size_t lds, hipStream_t st);
 // Lanes per candidate that the decision to draw ahead counts for a point mass.
 constexpr int kPmOverlapLanes = 8;
 // Workgroups that a drawing-ahead rollout launch adds at least.
