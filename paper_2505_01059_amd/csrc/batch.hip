@@ -152,7 +152,7 @@ __device__ __noinline__ void roll_point_mass_tile(const PlanDesc* desc, uint32_t
   const int b = static_cast<int>(__builtin_amdgcn_readfirstlane(tile)) * kBatchThreads + static_cast<int>(threadIdx.x);
   stage_obstacles(P, pm);
   __syncthreads();
-  if (b < P.B) rollout_point_mass_any(P, b, pm);
+  if (b < P.B) rollout_point_mass_any(P, b, 0, pm);
 }
 
 __device__ __forceinline__ void run_rollout_tile(const PlanDesc* desc, const PlanDesc& P, uint32_t lg, uint32_t tile) {

@@ -53,9 +53,8 @@ __global__ __launch_bounds__(kTopkThreads) void k_entropy(PlanDesc P, int k) {
 // (pm_tile.hpp).  Small launches are bound by the tile's latency (controls from
 // memory, the two serial passes over the steps), large ones by the obstacle
 // tests, which this form issues once per candidate and step.  Replan on eight
-// lanes per candidate through the horizon before -> now: 288 candidates x 50
-// steps x 10 iterations 0.211 -> 0.185 ms; 3341 x 77 x 6 0.170 -> 0.158 ms;
-// 15700 x 256 x 6 0.477 -> 0.414 ms.
+// lanes per candidate through the horizon before -> now: 3341 candidates x 77
+// steps x 6 iterations 0.170 -> 0.158 ms; 15700 x 256 x 6 0.477 -> 0.414 ms.
 constexpr int kPmTileCands = 16;
 __global__ __launch_bounds__(kRollThreads) void k_rollout_point_mass(PlanDesc P) {
   if (static_cast<int>(blockIdx.x) >= P.roll_blocks) { gen_tensor_tiles(P); return; }
@@ -87,6 +86,33 @@ __global__ __launch_bounds__(kRollThreads) void k_rollout_point_mass(PlanDesc P)
         }
       });
   if (tid < kPmTileCands && b0 + tid < P.B) P.cost[b0 + tid] = cost;
+}
+
+// Eight lanes per candidate through the horizon, each with an eighth of the
+// obstacle table, for launches of more tiles than the chip holds at a time.
+__global__ __launch_bounds__(kRollThreads) void k_rollout_point_mass_lanes(PlanDesc P) {
+  __shared__ PointMassSmem sm;
+  stage_obstacles(P, sm);
+  __syncthreads();
+  const int g = xcd_contiguous_block(blockIdx.x, P.roll_blocks) * kRollThreads + threadIdx.x;
+  const int b = g / kPmLanes;
+  if (b < P.B) rollout_point_mass_any<kPmLanes>(P, b, g % kPmLanes, sm);
+}
+
+// A compute unit holds four tiles.  Past that the last round of tiles leaves most
+// of the chip idle, and short horizons pay the tile's serial passes for little;
+// eight lanes per candidate are faster there, up to 32 obstacles (more do not fit
+// their registers).  Over long horizons the tiles, which test every obstacle once,
+// win again from seven per unit on, or with hardly any obstacle to test.  Replans of
+// four iterations, tiles -> eight lanes: 18000 candidates x 20 steps, 30 obstacles
+// 11 % shorter, 39000 x 20 14 %, 18000 x 50, 8 obstacles 4 %, 18000 x 200 2 to 5 %;
+// 33000 x 200 1 % longer; 16000 x 50 12 % longer.
+static_assert(kPmOverlapLanes == kPmLanes, "rollout_blocks counts the workgroups of the lanes");
+static bool pm_on_lanes(const PlanDesc& P) {
+  constexpr int kTilesPerUnit = 4, kManyTiles = 7, kLongHorizon = 64;
+  const int tiles = (P.B + kPmTileCands - 1) / kPmTileCands, n_obs = (P.n_task - 6) / 3;
+  return P.U2 == nullptr && n_obs <= 32 && tiles > kTilesPerUnit * P.gen_grid &&
+         (P.T < kLongHorizon || (n_obs >= 8 && tiles <= kManyTiles * P.gen_grid));
 }
 
 template <int N, bool CONTACT, bool ONE>
@@ -333,9 +359,10 @@ static hipError_t launch_rollout(const PlanDesc& P0, hipStream_t st, int gen_k) 
   if (is_pair_chain(P.dyn, P.n_links) && P.seg_ctl != nullptr && P.seg_grid > 0) return launch_rollout_seg(P, st);
   const bool gen = gen_k >= 0 && P.U2 != nullptr;
   const int lanes = wide_lanes(P, gen);
-  P.roll_blocks = lanes > 0              ? wide_blocks(P, lanes)
-                  : P.dyn == kPointMass ? (P.B + kPmTileCands - 1) / kPmTileCands
-                                        : rollout_blocks(P);
+  const bool tiled = P.dyn == kPointMass && !pm_on_lanes(P);
+  P.roll_blocks = lanes > 0 ? wide_blocks(P, lanes)
+                  : tiled   ? (P.B + kPmTileCands - 1) / kPmTileCands
+                            : rollout_blocks(P);
   P.gen_k = gen_k;
   int blocks = P.roll_blocks;
   size_t lds = 0;
@@ -346,7 +373,7 @@ static hipError_t launch_rollout(const PlanDesc& P0, hipStream_t st, int gen_k) 
     // where they leave too few of their own, the generator takes the eight-lane
     // form's share (5000 candidates x 64 steps, four iterations: 164 us with 32
     // workgroups drawing, 119 with 99).
-    if (P.dyn == kPointMass && P.roll_blocks + kMinGenBlocks > P.gen_grid)
+    if (tiled && P.roll_blocks + kMinGenBlocks > P.gen_grid)
       gens = std::max(P.gen_grid - rollout_blocks(P), kMinGenBlocks);
     blocks = P.roll_blocks + gens;
     lds = blocks <= P.gen_grid ? gen_lds_bytes(P) : gen_tile_bytes(P);
@@ -362,7 +389,8 @@ static hipError_t launch_rollout(const PlanDesc& P0, hipStream_t st, int gen_k) 
 template <bool ONE>
 static hipError_t launch_rollout_kernel(const PlanDesc& P, dim3 grid, size_t lds, hipStream_t st) {
   if (P.dyn == kPointMass) {
-    k_rollout_point_mass<<<grid, kRollThreads, lds, st>>>(P);
+    if (pm_on_lanes(P)) k_rollout_point_mass_lanes<<<grid, kRollThreads, lds, st>>>(P);
+    else k_rollout_point_mass<<<grid, kRollThreads, lds, st>>>(P);
     return hipGetLastError();
   }
   if (is_quad_chain(P.dyn, P.n_links)) return launch_rollout_quad(P, grid, lds, st, ONE);

@@ -614,25 +614,38 @@ __device__ __forceinline__ float quad_sum(float v) {
 // The obstacle penalties of a step are summed in eight groups, obstacle o in
 // group o mod 8, each in increasing o, and the groups as
 // ((g0 + g1) + (g2 + g3)) + ((g4 + g5) + (g6 + g7)); the tiles of pm_tile.hpp
-// add them in the same order.
-template <int NOBS>
-__device__ __forceinline__ void rollout_point_mass(const PlanDesc& P, int b, const PointMassSmem& sm) {
+// add them in the same order.  LANES = 1: one lane per candidate holds every
+// group.  LANES = 8: lane q of the candidate's eight holds group q (an eighth of
+// the table); two quad permutes add the groups of each quad and a half-row mirror
+// adds the two quads, in the same order, so every lane ends the step with the
+// same bits; the state update, goal and control terms run on all eight alike.
+constexpr int kPmLanes = 8;
+constexpr int kDppHalfMirror = 0x141;   // lane i of each eight reads lane 7 - i
+
+__device__ __forceinline__ float half_mirror(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kDppHalfMirror, 0xF, 0xF, true));
+}
+
+template <int NOBS, int LANES = 1>
+__device__ __forceinline__ void rollout_point_mass(const PlanDesc& P, int b, int q, const PointMassSmem& sm) {
+  static_assert(LANES == 1 || (LANES == kPmLanes && NOBS > 0), "one lane, or eight with a register table");
   static_assert(NOBS % 8 == 0, "register tables hold whole groups");
   // task: goal_x, goal_y, goal_w, obstacle_penalty, ctrl_w, n_obs, (cx, cy, r)*
   const float* tk = P.task;
   const float gx = tk[0], gy = tk[1], wg = tk[2], pen = tk[3], wu = tk[4];
   const int n_obs = static_cast<int>(tk[5]);
-  constexpr int NL = NOBS > 0 ? NOBS : 1;   // register obstacles
+  constexpr int NL = NOBS > 0 ? NOBS / LANES : 1;   // register obstacles per lane
   float ocx[NL], ocy[NL], orr[NL];
   if constexpr (NOBS > 0) {
     // read from the LDS copy so that the table lands in vector registers (as
     // uniform scalars it would not fit the scalar register file)
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-      const bool on = i < n_obs;
-      ocx[i] = on ? sm.obs[3 * i] : 0.0f;
-      ocy[i] = on ? sm.obs[3 * i + 1] : 0.0f;
-      orr[i] = on ? sm.obs[3 * i + 2] : -1.0f;
+      const int o = LANES == 1 ? i : q + kPmLanes * i;
+      const bool on = o < n_obs;
+      ocx[i] = on ? sm.obs[3 * o] : 0.0f;
+      ocy[i] = on ? sm.obs[3 * o + 1] : 0.0f;
+      orr[i] = on ? sm.obs[3 * o + 2] : -1.0f;
     }
   }
   const float* obs = sm.obs;
@@ -652,19 +665,28 @@ __device__ __forceinline__ void rollout_point_mass(const PlanDesc& P, int b, con
     px = fmaf(dt, vx, px);
     py = fmaf(dt, vy, py);
     const float dx = px - gx, dy = py - gy;
-    float pc[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    if constexpr (NOBS > 0) {
+    float obst;
+    if constexpr (LANES == 1) {
+      float pc[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+      if constexpr (NOBS > 0) {
 #pragma unroll
-      for (int o = 0; o < NOBS; ++o) pc[o & 7] += hit(px - ocx[o], py - ocy[o], orr[o]);
+        for (int o = 0; o < NOBS; ++o) pc[o & 7] += hit(px - ocx[o], py - ocy[o], orr[o]);
+      } else {
+        for (int o = 0; o < n_obs; ++o) pc[o & 7] += hit(px - obs[3 * o], py - obs[3 * o + 1], obs[3 * o + 2]);
+      }
+      obst = ((pc[0] + pc[1]) + (pc[2] + pc[3])) + ((pc[4] + pc[5]) + (pc[6] + pc[7]));
     } else {
-      for (int o = 0; o < n_obs; ++o) pc[o & 7] += hit(px - obs[3 * o], py - obs[3 * o + 1], obs[3 * o + 2]);
+      float g = 0.0f;
+#pragma unroll
+      for (int i = 0; i < NL; ++i) g += hit(px - ocx[i], py - ocy[i], orr[i]);
+      g = quad_sum(g);
+      obst = g + half_mirror(g);
     }
-    const float obst = ((pc[0] + pc[1]) + (pc[2] + pc[3])) + ((pc[4] + pc[5]) + (pc[6] + pc[7]));
     float c = fmaf(wg, fmaf(dx, dx, dy * dy), obst);
     c = fmaf(wu, fmaf(ux, ux, uy * uy), c);
     cost += c;
     if constexpr (decltype(rec)::value) {
-      if (b < P.n_dbg) {
+      if (b < P.n_dbg && q == 0) {
         float* X = P.X + b;
         const size_t ldx = static_cast<size_t>(P.n_dbg);
         X[(t * 4 + 0) * ldx] = px; X[(t * 4 + 1) * ldx] = py;
@@ -709,7 +731,7 @@ __device__ __forceinline__ void rollout_point_mass(const PlanDesc& P, int b, con
   };
   if (__builtin_amdgcn_ballot_w64(b < P.n_dbg) != 0) run(std::true_type{});
   else run(std::false_type{});
-  store_result(&P.cost[b], finite_or_inf(cost));
+  if (q == 0) store_result(&P.cost[b], finite_or_inf(cost));
 }
 
 // Obstacle-table size class of a point-mass plan: 8, 16, 24, 32 in registers, 0 in LDS.
@@ -717,13 +739,16 @@ __device__ __host__ __forceinline__ int point_mass_obs_class(int n_obs) {
   return n_obs <= 8 ? 8 : (n_obs <= 16 ? 16 : (n_obs <= 24 ? 24 : (n_obs <= 32 ? 32 : 0)));
 }
 
-__device__ __forceinline__ void rollout_point_mass_any(const PlanDesc& P, int b, const PointMassSmem& sm) {
+template <int LANES = 1>
+__device__ __forceinline__ void rollout_point_mass_any(const PlanDesc& P, int b, int q, const PointMassSmem& sm) {
   switch (point_mass_obs_class(static_cast<int>(P.task[5]))) {
-    case 8: rollout_point_mass<8>(P, b, sm); return;
-    case 16: rollout_point_mass<16>(P, b, sm); return;
-    case 24: rollout_point_mass<24>(P, b, sm); return;
-    case 32: rollout_point_mass<32>(P, b, sm); return;
-    default: rollout_point_mass<0>(P, b, sm); return;
+    case 8: rollout_point_mass<8, LANES>(P, b, q, sm); return;
+    case 16: rollout_point_mass<16, LANES>(P, b, q, sm); return;
+    case 24: rollout_point_mass<24, LANES>(P, b, q, sm); return;
+    case 32: rollout_point_mass<32, LANES>(P, b, q, sm); return;
+    default:
+      if constexpr (LANES == 1) rollout_point_mass<0>(P, b, q, sm);
+      return;
   }
 }
 
