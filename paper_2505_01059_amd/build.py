@@ -23,12 +23,14 @@ def _sched(strategy):
 # a wave's latency shows, and each form has an order that suits it.  Launches in us
 # with LLVM's default / iterative-ilp / max-ilp scheduler (values are the same):
 # time-sliced 24 links in contact 2910 / 2945 / 2900; one lane, 4 links, 40000
-# candidates 80 / 76 / 76; four lanes, 12 links 89 / 92 / 86; eight lanes, 24 links
-# 121 / 122 / 115; four lanes, 24 links in contact 748 / 760 / 762; four lanes, 7
-# links in contact, three models 168 / 161 / 168; four lanes, 4 links 55.6 / 58.0 /
+# candidates 80 / 76 / 76, 3 links, 600, 5000 and 40000 candidates 55.3 / 55.9 / 57.0,
+# 55.2 / 56.0 / 57.3 and 55.9 / 56.5 / 57.6, 2 links 38.8 / 39.4 / 39.0, 39.7 / 39.7 /
+# 38.7 and 40.5 / 40.1 / 38.8; four lanes, 12 links 89 / 92 / 86; eight lanes, 24
+# links 121 / 122 / 115; four lanes, 24 links in contact 748 / 760 / 762; four lanes,
+# 7 links in contact, three models 168 / 161 / 168; four lanes, 4 links 55.6 / 58.0 /
 # 55.9; quad lanes, 7 links 109.5 / 110.8 / 110.6, but as long as their generator
-# 200 / 145 / 200 (14000 candidates, a unit of its own).  Whole point-mass replans 75.8 /
-# 74.4 / 74.8 us; 256 instances batched 77.1 / 76.7 / 76.9 ms.
+# 200 / 145 / 200 (14000 candidates, a unit of its own).  Whole point-mass replans
+# 75.8 / 74.4 / 74.8 us; 256 instances batched 77.1 / 76.7 / 76.9 ms.
 EXTRA_FLAGS = {
     "batch.hip": _sched("iterative-ilp"),
     "pm_replan.hip": _sched("iterative-ilp"),

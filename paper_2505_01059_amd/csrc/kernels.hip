@@ -412,7 +412,24 @@ static hipError_t launch_rollout_kernel(const PlanDesc& P, dim3 grid, size_t lds
     }
     return hipErrorInvalidValue;
   }
-  if (P.dyn == kChain) return launch_rollout_line(P, grid, lds, st, ONE);
+  if (P.dyn == kChain) {
+    // Two and three links: the rollout is shorter under this unit's option, the
+    // generator under the other's.  Rollouts alone, us here and there: 3 links, 250
+    // candidates x 96 steps 80.0 and 81.8, 40000 x 64 55.9 and 56.5; 2 links, 1100 x
+    // 50 31.2 and 32.3, 20000 x 64 40.8 and 40.0.  Replans of four iterations with
+    // the generator, 3 links, 600 x 32 154.4 and 152.5, 39000 x 16 260 and 250, 20000
+    // x 256 990 and 1015.
+    const bool alone = static_cast<int>(grid.x) == P.roll_blocks;
+    const bool here = P.n_links == 3 ? alone || P.T >= 96 : P.n_links == 2 && alone && P.B <= 8192;
+    if (!here) return launch_rollout_line(P, grid, lds, st);
+    switch (P.n_links) {
+#define X(N) case N: if constexpr (N <= 3) { k_rollout_chain<N, false, ONE><<<grid, kRollThreads, lds, st>>>(P); return hipGetLastError(); } break;
+      MTP_CHAIN_LINKS(X)
+#undef X
+      default: break;
+    }
+    return hipErrorInvalidValue;
+  }
   switch (P.n_links) {
 #define X(N) case N: if constexpr (!pair_chain_links<N>()) { k_rollout_chain<N, true, ONE><<<grid, kRollThreads, lds, st>>>(P); return hipGetLastError(); } break;
     MTP_CONTACT_LINKS(X)

@@ -48,8 +48,8 @@ int wide_blocks(const PlanDesc& P, int lanes);
 hipError_t launch_rollout_wide(const PlanDesc& P, int lanes, dim3 grid, size_t lds, hipStream_t st, bool one);
 hipError_t launch_wide_half(const PlanDesc& P, int lanes, dim3 grid, size_t lds, hipStream_t st, bool one);
 hipError_t launch_wide_rest(const PlanDesc& P, int lanes, dim3 grid, size_t lds, hipStream_t st, bool one);
-// One-lane rollouts of the short chains without contact (rollout_line.hip).
-hipError_t launch_rollout_line(const PlanDesc& P, dim3 grid, size_t lds, hipStream_t st, bool one);
+// One-lane rollouts without contact (rollout_line.hip).
+hipError_t launch_rollout_line(const PlanDesc& P, dim3 grid, size_t lds, hipStream_t st);
 // LDS a time-sliced rollout asks for, so that no two of its workgroups share a
 // compute unit: more than half of the unit's 160 KB, leaving room for a
 // generator workgroup (k_gen_tensor).  From 20 links on the registers see to it.

@@ -1,5 +1,5 @@
-// Device pieces shared by the single-plan rollout kernels (kernels.hip and
-// rollout_quad.hip): the block remap, the tensor-path generator run by the
+// Device pieces shared by the single-plan rollout kernels (kernels.hip and the
+// rollout_*.hip units): the block remap, the tensor-path generator run by the
 // workgroups a rollout launch adds, and the occupancy target of the two builds.
 #pragma once
 
@@ -46,8 +46,9 @@ __device__ __forceinline__ void gen_tensor_tiles(const PlanDesc& P) {
 // in flight); otherwise the usual occupancy target.
 #define MTP_ROLL_WAVES(one) __attribute__((amdgpu_waves_per_eu(1, (one) ? 1 : 8)))
 
-// One candidate per lane: the chains too short for the other narrow forms.
-template <int N, bool CONTACT, bool ONE>
+// One candidate per lane: the chains too short for the other narrow forms.  LINE
+// keeps the kernels of rollout_line.hip apart from those of kernels.hip.
+template <int N, bool CONTACT, bool ONE, bool LINE = false>
 __global__ __launch_bounds__(kRollThreads) MTP_ROLL_WAVES(ONE) void k_rollout_chain(PlanDesc P) {
   if (static_cast<int>(blockIdx.x) >= P.roll_blocks) { gen_tensor_tiles(P); return; }
   const int b = xcd_contiguous_block(blockIdx.x, P.roll_blocks) * kRollThreads + threadIdx.x;
