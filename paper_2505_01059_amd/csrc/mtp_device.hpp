@@ -80,7 +80,7 @@ struct PlanDesc {
   int32_t gen_spec;      // this generator launch draws for replan ctrl[0] + 1, iteration 0, leaving Z and I
   int32_t cand_skip;     // this candidate launch leaves the tensor paths when ctrl[4] is set
   int32_t gen_grid;      // compute units: workgroups of such a launch (one per unit)
-  float* pm_cost;        // [K][P] tensor-path costs of every iteration (whole point-mass replans, or null)
+  float* pm_cost;        // [min(K, kPmChunk)][P] tensor-path costs by iteration (whole point-mass replans, or null)
 };
 
 // Sizes that a whole point-mass replan (pm_replan.hip) holds on one compute unit.
@@ -91,6 +91,7 @@ constexpr int kPmLocal = 32;         // local candidates
 constexpr int kPmElites = 64;        // one per lane of a wave
 constexpr int kPmValues = 9216;      // elite controls 2 T E
 constexpr int kPmCands = 1024;       // candidates
+constexpr int kPmChunk = 64;         // iterations per launch: at most 256 KB of kept costs
 
 // ------------------------------------------------------------------ Philox
 // Philox4x32-10 from Salmon et al., SC'11: ten rounds of two 32x32->64-bit

@@ -158,7 +158,7 @@ Layout compute_layout(const mtp_config& c, bool plan) {
   L.overlap = plan && uses_gen_overlap(c);
   L.U2 = L.overlap ? take(T * n * L.ldU * 4) : 0;
   L.pm = plan && uses_pm_replan(c);
-  L.pm_cost = L.pm ? take(static_cast<size_t>(c.n_iters) * std::max(c.n_tensor, 1) * 4) : 0;
+  L.pm_cost = L.pm ? take(static_cast<size_t>(std::min(c.n_iters, kPmChunk)) * std::max(c.n_tensor, 1) * 4) : 0;
   L.transient = off;
   L.total = L.resident + L.transient;
   return L;

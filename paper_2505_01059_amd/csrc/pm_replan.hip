@@ -8,7 +8,8 @@
 // costs and the refit, is small enough for one workgroup: k_pm_iterate runs all
 // iterations with workgroup barriers between the stages instead of launches.
 // Every operation and its order are those of the staged kernels, so the results
-// are the same bits.
+// are the same bits.  Long replans run in chunks of kPmChunk iterations, so that
+// the kept costs and a launch's time stay bounded.
 //
 // What bounds an iteration is the latency of its chain (about ten dependent
 // phases on one compute unit); the normals and the graph of the next iteration
@@ -96,6 +97,18 @@ __device__ __forceinline__ float tensor_control(const PlanDesc& P, const float* 
   return clampf(v, P.u_min, P.u_max);
 }
 
+// What a launch runs: all iterations, or a range (kernels of its own: with the
+// bounds as values whole replans take 1 to 2 % longer).
+struct WholeReplan {
+  __device__ int begin(const PlanDesc&) const { return 0; }
+  __device__ int end(const PlanDesc& P) const { return P.K; }
+};
+struct IterRange {
+  int k0, k1;
+  __device__ int begin(const PlanDesc&) const { return k0; }
+  __device__ int end(const PlanDesc&) const { return k1; }
+};
+
 // ------------------------------------------------------------------ tensor paths of all iterations
 struct TensorSmem {
   PmTile<kTensorTile> tile;
@@ -106,14 +119,15 @@ struct TensorSmem {
   float ctp[kMaxLayers][2][kTensorTile], slp[kMaxLayers][2][kTensorTile];   // control points, Akima slopes
 };
 
-// Workgroup (tile, k): the costs of tensor paths 16 tile .. of iteration k; the
-// last iteration's also leave their controls, indices and graph where the
+// Workgroup (tile, i): the costs of tensor paths 16 tile .. of the range's iteration i;
+// the last iteration's also leave their controls, indices and graph where the
 // staged kernels do.  Workgroup (0, 0) records the replan (as k_set_ctrl).
+template <class Range>
 __global__ __launch_bounds__(kTensorThreads) void k_pm_tensor(PlanDesc P, uint32_t r, int shift,
-                                                              const float* __restrict__ x0_src) {
+                                                              const float* __restrict__ x0_src, Range range) {
   __shared__ TensorSmem sm;
   const int tid = threadIdx.x;
-  const int k = blockIdx.y;
+  const int k = range.begin(P) + static_cast<int>(blockIdx.y);
   const bool keep = k == P.K - 1;
   if (blockIdx.x == 0 && k == 0) {
     if (tid < 4) P.x0[tid] = x0_src[tid];
@@ -166,7 +180,7 @@ __global__ __launch_bounds__(kTensorThreads) void k_pm_tensor(PlanDesc P, uint32
     }
   }, [](int, int, int, float, float) {});
   if (tid < kTensorTile && p0 + tid < P.P) {
-    P.pm_cost[static_cast<size_t>(k) * P.P + p0 + tid] = cost;
+    P.pm_cost[static_cast<size_t>(blockIdx.y) * P.P + p0 + tid] = cost;
     if (keep) P.cost[P.G - 1 + p0 + tid] = cost;
   }
 }
@@ -202,8 +216,10 @@ struct IterSmem {
   float ctp[kMaxLayers][2][kPmElites], slp[kMaxLayers][2][kPmElites];   // the elites' control points, Akima slopes
 };
 
-template <int C>
-__global__ __launch_bounds__(kIterThreads) void k_pm_iterate(PlanDesc P) {
+// The iterations of the range, from the moments that the previous ones left.
+template <int C, class Range>
+__global__ __launch_bounds__(kIterThreads) void k_pm_iterate(PlanDesc P, Range range) {
+  const int k0 = range.begin(P), k1 = range.end(P);
   __shared__ IterSmem<C> sm;
   int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -226,8 +242,8 @@ __global__ __launch_bounds__(kIterThreads) void k_pm_iterate(PlanDesc P) {
   for (int i = tid; i < P.T; i += kIterThreads) sm.ts[i] = P.span[i];
   for (int i = tid; i < P.T * kBasisStride; i += kIterThreads) sm.tb[i] = P.basis[i];
   {
-    // the warm start, shifted (as shift_block)
-    const int s = min(static_cast<int>(P.ctrl[1]), P.T);
+    // the warm start, shifted (as shift_block), or the moments as they are
+    const int s = k0 == 0 ? min(static_cast<int>(P.ctrl[1]), P.T) : 0;
     for (int e = tid; e < Tn; e += kIterThreads) {
       const int t = e >> 1, j = e & 1;
       sm.mu[0][e] = P.mu[s == 0 ? e : (t < P.T - s ? e + 2 * s : (P.T - 1) * 2 + j)];
@@ -236,21 +252,21 @@ __global__ __launch_bounds__(kIterThreads) void k_pm_iterate(PlanDesc P) {
   }
   // tensor paths' cost images of iteration k
   auto take_tensor = [&](int k, uint32_t* image, int first, int stride) {
-    for (int p = first; p < P.P; p += stride) image[G1 + p] = cost_order(P.pm_cost[static_cast<size_t>(k) * P.P + p]);
+    for (int p = first; p < P.P; p += stride) image[G1 + p] = cost_order(P.pm_cost[static_cast<size_t>(k - k0) * P.P + p]);
   };
   for (int b = P.B + tid; b < 64 * kWaveKeys; b += kIterThreads) sm.image[0][b] = sm.image[1][b] = 0xFFFFFFFFu;
-  take_tensor(0, sm.image[0], tid, kIterThreads);
-  draw_graph(P, r, 0, sm.z[0], tid, kIterThreads);
-  draw_normals(0, sm.normals[0], tid, kIterThreads);
+  take_tensor(k0, sm.image[0], tid, kIterThreads);
+  draw_graph(P, r, k0, sm.z[0], tid, kIterThreads);
+  draw_normals(k0, sm.normals[0], tid, kIterThreads);
   __syncthreads();
 
-  for (int k = 0; k < P.K; ++k) {
+  for (int k = k0; k < k1; ++k) {
     // addresses and masks are made again in every iteration: kept across them
     // they do not fit the registers, and each use would wait for its reload
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63;
-    const int cur = k & 1;          // buffers of this iteration; the others are the next one's
-    const bool last = k == P.K - 1;
+    const int cur = (k - k0) & 1;   // buffers of this iteration; the others are the next one's
+    const bool stop = k == k1 - 1, last = stop && k1 == P.K;   // the launch's last, the replan's
     const float* mu = sm.mu[cur];
     const float* sg = sm.sg[cur];
     const float* nz = sm.normals[cur];
@@ -297,7 +313,7 @@ __global__ __launch_bounds__(kIterThreads) void k_pm_iterate(PlanDesc P) {
       }
       if (lane == 0 && !(s0 < INFINITY)) atomicOr(&P.ctrl[2], 1u);
       __builtin_amdgcn_s_setprio(0);
-    } else if (!last && (wave & 3) != 0) {
+    } else if (!stop && (wave & 3) != 0) {
       // the waves of the other three SIMDs prepare the next iteration meanwhile
       const int first = (wave - 1 - (wave >> 2)) * 64 + lane;
       constexpr int kHelpers = kIterThreads / 4 * 3;
@@ -367,10 +383,10 @@ __global__ __launch_bounds__(kIterThreads) void k_pm_iterate(PlanDesc P) {
       if (s == 0 && (a >> 2) < Tn) {
         sm.mu[cur ^ 1][o] = mn;
         sm.sg[cur ^ 1][o] = sn;
-        if (last) {
+        if (stop) {
           P.mu[o] = mn;
           P.sigma[o] = sn;
-          if (o < 2) P.action[o] = val[0];
+          if (o < 2) P.action[o] = val[0];   // the last chunk's is the replan's
         }
       }
     }
@@ -378,18 +394,30 @@ __global__ __launch_bounds__(kIterThreads) void k_pm_iterate(PlanDesc P) {
   }
 }
 
-}  // namespace
-
-hipError_t launch_pm_replan(const PlanDesc& P, uint32_t r, int shift, const float* x0_src, hipStream_t st) {
-  const dim3 grid(std::max(1, (P.P + kTensorTile - 1) / kTensorTile), P.K);
-  k_pm_tensor<<<grid, kTensorThreads, 0, st>>>(P, r, shift, x0_src);
+template <class Range>
+hipError_t launch_range(const PlanDesc& P, uint32_t r, int shift, const float* x0_src, int iters, Range range,
+                        hipStream_t st) {
+  const dim3 grid(std::max(1, (P.P + kTensorTile - 1) / kTensorTile), iters);
+  k_pm_tensor<<<grid, kTensorThreads, 0, st>>>(P, r, shift, x0_src, range);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // the tile's width follows the local candidates: idle lanes cost as much as others
-  if (P.G <= 4) k_pm_iterate<4><<<1, kIterThreads, 0, st>>>(P);
-  else if (P.G <= 16) k_pm_iterate<16><<<1, kIterThreads, 0, st>>>(P);
-  else k_pm_iterate<kPmLocal><<<1, kIterThreads, 0, st>>>(P);
+  if (P.G <= 4) k_pm_iterate<4><<<1, kIterThreads, 0, st>>>(P, range);
+  else if (P.G <= 16) k_pm_iterate<16><<<1, kIterThreads, 0, st>>>(P, range);
+  else k_pm_iterate<kPmLocal><<<1, kIterThreads, 0, st>>>(P, range);
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_pm_replan(const PlanDesc& P, uint32_t r, int shift, const float* x0_src, hipStream_t st) {
+  if (P.K <= kPmChunk) return launch_range(P, r, shift, x0_src, P.K, WholeReplan{}, st);
+  for (int k0 = 0; k0 < P.K; k0 += kPmChunk) {
+    const int k1 = std::min(k0 + kPmChunk, P.K);
+    const hipError_t e = launch_range(P, r, shift, x0_src, k1 - k0, IterRange{k0, k1}, st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace mtp
