@@ -377,9 +377,12 @@ mtp_status mtp_schedule_cache_store(const char* path, const char* arch, int32_t 
 /* Scheduling of the batched launch: the items a launch of all these instances on
  * `workgroups` persistent workgroups is cut into under a schedule, and the
  * estimates they are chosen by (one CEM iteration of the instance, chosen items
- * and the launch's plain ones).  Host only; h_out receives n entries. */
+ * and the launch's plain ones).  queue_items: the queue's length, 0 = as long as
+ * needed; where it is too short, instances keep the plain items, those first that
+ * would save the least time per item.  Host only; h_out receives n entries. */
 typedef struct {
   int32_t finest;         /* the finest items (see split_pct), else the schedule's */
+  uint32_t items;         /* queue items of all its iterations */
   int32_t wide_lg;        /* log2 of the rollout's lanes per candidate over the narrow form */
   double path_us;         /* the instance's stages in turn, with every workgroup its own */
   double plain_path_us;
@@ -387,7 +390,8 @@ typedef struct {
   double plain_work_us;
 } mtp_batch_items;
 mtp_status mtp_batch_item_shapes(const mtp_config* cfgs, int32_t n, int32_t workgroups,
-                                 const mtp_batch_schedule* h_schedule, mtp_batch_items* h_out);
+                                 const mtp_batch_schedule* h_schedule, uint64_t queue_items,
+                                 mtp_batch_items* h_out);
 /* As mtp_set_graph_mode, for the persistent launch. */
 mtp_status mtp_batch_set_graph_mode(mtp_batch* b, int32_t use_graph);
 /* Release the batch object (the workspace stays the caller's). */

@@ -104,7 +104,7 @@ def load():
         "mtp_batch_get_schedule": (c_int32, [P, P]),
         "mtp_batch_tune": (c_int32, [P, c_int32, c_char_p, P, POINTER(c_float), POINTER(c_int32)]),
         "mtp_batch_mix_signature": (c_uint64, [P, c_int32]),
-        "mtp_batch_item_shapes": (c_int32, [P, c_int32, c_int32, P, P]),
+        "mtp_batch_item_shapes": (c_int32, [P, c_int32, c_int32, P, c_uint64, P]),
         "mtp_schedule_cache_lookup": (c_int32, [c_char_p, c_char_p, c_int32, c_uint64, P, POINTER(c_float),
                                                 POINTER(c_int32)]),
         "mtp_schedule_cache_store": (c_int32, [c_char_p, c_char_p, c_int32, c_uint64, P, c_float]),
@@ -430,11 +430,11 @@ def _schedule_struct(d):
 
 
 class mtp_batch_items(ctypes.Structure):
-    _fields_ = [("finest", c_int32), ("wide_lg", c_int32), ("path_us", ctypes.c_double),
+    _fields_ = [("finest", c_int32), ("items", c_uint32), ("wide_lg", c_int32), ("path_us", ctypes.c_double),
                 ("plain_path_us", ctypes.c_double), ("work_us", ctypes.c_double), ("plain_work_us", ctypes.c_double)]
 
 
-def batch_item_shapes(cfgs, workgroups, **knobs):
+def batch_item_shapes(cfgs, workgroups, queue_items=0, **knobs):
     """mtp_batch_item_shapes of a list of workload configs (host only), one dict per instance; knobs: schedule
     fields other than the defaults of mtp.h."""
     lib = load()
@@ -446,7 +446,8 @@ def batch_item_shapes(cfgs, workgroups, **knobs):
             raise ValueError(f"unknown schedule knob {k}")
         setattr(s, k, int(v))
     out = (mtp_batch_items * len(structs))()
-    _check(lib, lib.mtp_batch_item_shapes(arr, len(structs), int(workgroups), byref(s), out))
+    _check(lib, lib.mtp_batch_item_shapes(arr, len(structs), int(workgroups), byref(s), int(queue_items),
+                                          out))
     return [{name: getattr(o, name) for name, _ in mtp_batch_items._fields_} for o in out]
 
 

@@ -9,6 +9,7 @@
 #include <new>
 #include <numeric>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/mtp.h"
@@ -166,6 +167,35 @@ std::vector<uint32_t> choose_shapes(const std::vector<LaunchPart>& parts, int wo
     }
   }
   return shapes;
+}
+
+// Fits the shapes into a queue of `capacity` items (a queue sized by its owner):
+// while they need more, instances go back to the plain shape, those first that
+// save the least time per item.  Returns the items needed.
+uint64_t fit_shapes(const std::vector<LaunchPart>& parts, int workgroups, uint32_t plain, uint64_t capacity,
+                    std::vector<uint32_t>* shapes) {
+  std::vector<int64_t> extra(parts.size(), 0);
+  uint64_t total = 0;
+  for (size_t a = 0; a < parts.size(); ++a) {
+    const uint32_t items = items_for(*parts[a].cfg, 0, parts[a].iters, (*shapes)[a]);
+    extra[a] = static_cast<int64_t>(items) - items_for(*parts[a].cfg, 0, parts[a].iters, plain);
+    total += items;
+  }
+  if (total <= capacity) return total;
+  std::vector<std::pair<double, size_t>> order;   // us saved per item
+  for (size_t a = 0; a < parts.size(); ++a)
+    if (extra[a] > 0) {
+      const double saved = stage_cost(*parts[a].cfg, plain, workgroups).path -
+                           stage_cost(*parts[a].cfg, (*shapes)[a], workgroups).path;
+      order.emplace_back(saved * parts[a].iters / static_cast<double>(extra[a]), a);
+    }
+  std::sort(order.begin(), order.end());
+  for (size_t i = 0; i < order.size() && total > capacity; ++i) {
+    const size_t a = order[i].second;
+    (*shapes)[a] = plain;
+    total -= static_cast<uint64_t>(extra[a]);
+  }
+  return total;
 }
 
 struct BatchLayout {
@@ -680,18 +710,9 @@ mtp_status mtp_batch_step(mtp_batch* b, int32_t n_active, const int32_t* h_activ
   }
   std::vector<LaunchPart> parts(n_active);
   for (int a = 0; a < n_active; ++a) parts[a] = {&b->cfgs[h_active[a]], h_k_end[a] - h_k_begin[a]};
-  uint32_t shape = 0;
-  std::vector<uint32_t> shapes = choose_shapes(parts, b->grid, b->sched, &shape);
-  auto count = [&]() {
-    uint64_t sum = 0;
-    for (int a = 0; a < n_active; ++a) sum += items_for(b->cfgs[h_active[a]], h_k_begin[a], h_k_end[a], shapes[a]);
-    return sum;
-  };
-  uint64_t total = count();
-  if (total > b->lay.capacity) {   // a queue sized by its owner: the plain shape needs the fewest items of those chosen
-    shapes.assign(n_active, shape);
-    total = count();
-  }
+  uint32_t plain = 0;
+  std::vector<uint32_t> shapes = choose_shapes(parts, b->grid, b->sched, &plain);
+  const uint64_t total = fit_shapes(parts, b->grid, plain, b->lay.capacity, &shapes);
   for (int a = 0; a < n_active; ++a) b->h_ictl[h_active[a]].shape = shapes[a];
   if (total > b->lay.capacity) {
     b->err = "step needs more queue items than the batch was sized for";
@@ -781,7 +802,7 @@ mtp_status mtp_batch_get_schedule(const mtp_batch* b, mtp_batch_schedule* h_sche
 }
 
 mtp_status mtp_batch_item_shapes(const mtp_config* cfgs, int32_t n, int32_t workgroups,
-                                 const mtp_batch_schedule* h_schedule, mtp_batch_items* h_out) {
+                                 const mtp_batch_schedule* h_schedule, uint64_t queue_items, mtp_batch_items* h_out) {
   if (cfgs == nullptr || n < 1 || workgroups < 1 || h_schedule == nullptr || h_out == nullptr ||
       !schedule_valid(*h_schedule))
     return MTP_ERR_INVALID_ARG;
@@ -792,8 +813,10 @@ mtp_status mtp_batch_item_shapes(const mtp_config* cfgs, int32_t n, int32_t work
     parts[i] = {&cfgs[i], cfgs[i].n_iters};
   }
   uint32_t plain = 0;
-  const std::vector<uint32_t> shapes = choose_shapes(parts, workgroups, *h_schedule, &plain);
+  std::vector<uint32_t> shapes = choose_shapes(parts, workgroups, *h_schedule, &plain);
+  if (queue_items > 0) (void)fit_shapes(parts, workgroups, plain, queue_items, &shapes);
   for (int32_t i = 0; i < n; ++i) {
+    h_out[i].items = items_for(cfgs[i], 0, cfgs[i].n_iters, shapes[i]);
     h_out[i].finest = (shapes[i] & ~make_shape(0, 0, 0, 0, 3)) == kShapeFinest ? 1 : 0;
     h_out[i].wide_lg = static_cast<int32_t>(shape_wide_lg(shapes[i]));
     h_out[i].path_us = stage_cost(cfgs[i], shapes[i], workgroups).path;

@@ -59,6 +59,25 @@ def test_never_split_keeps_the_plain_shape():
             assert it["finest"] == 0 and it["wide_lg"] == 0 and it["path_us"] == it["plain_path_us"]
 
 
+@pytest.mark.parametrize("name", ["mixed", "fleet of 4", "fleet of 24", "mix of 32"])
+def test_a_short_queue_takes_back_only_what_does_not_fit(name):
+    cfgs = SETS[name]
+    full = mtp.batch_item_shapes(cfgs, UNITS)
+    need = sum(it["items"] for it in full)
+    plain = sum(it["items"] for it in mtp.batch_item_shapes(cfgs, UNITS, queue_items=1))   # every instance plain
+    split = [i for i, it in enumerate(full) if it["path_us"] < it["plain_path_us"]]
+    assert plain < need and split
+    assert mtp.batch_item_shapes(cfgs, UNITS, queue_items=need) == full
+    for room in (need - 1, (need + plain) // 2, plain):
+        got = mtp.batch_item_shapes(cfgs, UNITS, queue_items=room)
+        assert sum(it["items"] for it in got) <= room
+        kept = [i for i in split if got[i] == full[i]]
+        assert len(kept) == (len(split) - 1 if room == need - 1 else len(kept))
+        for i in range(len(cfgs)):
+            assert got[i] == full[i] or got[i]["path_us"] == got[i]["plain_path_us"]
+    assert kept == []
+
+
 def test_bad_arguments_are_refused():
     with pytest.raises(mtp.MtpError):
         mtp.batch_item_shapes(SETS["small"], 0)
