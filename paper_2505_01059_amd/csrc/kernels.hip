@@ -131,9 +131,13 @@ __global__ __launch_bounds__(kRollThreads) MTP_ROLL_WAVES(ONE || N >= 20) void k
 // registers free on every unit whichever kernel is dispatched first.
 __global__ __launch_bounds__(kCandThreads) void k_gen_tensor(PlanDesc P) { gen_tensor_tiles(P); }
 
+// The small selection in a kernel of its own: beside the other it cost 1 us of it.
+static TopkSizes topk_sizes(const PlanDesc& P) { return P.B <= kTopkBoundary ? kTopkSmall : kTopkLarge; }
+
+template <TopkSizes SIZES>
 __global__ __launch_bounds__(kTopkThreads) void k_topk(PlanDesc P) {
   __shared__ TopkSmem sm;
-  topk_block<kTopkThreads>(P, sm);
+  topk_block<kTopkThreads, false, SIZES>(P, sm);
 }
 
 __global__ __launch_bounds__(kUpdThreads) void k_update(PlanDesc P) {
@@ -210,7 +214,7 @@ __global__ __launch_bounds__(kUpdThreads) void k_refit_regen(PlanDesc P, int k, 
 // 9216 x 7 x 8 1.020 -> 1.002 ms; 3376 x 12 x 6 0.631 -> 0.621 ms; 3341 point
 // masses x 6 153.3 -> 146.2 us; 13500 x 4 x 4 0.310 -> 0.303 ms.
 constexpr int kFusedThreads = kTopkThreads;
-template <bool NEXT>
+template <bool NEXT, TopkSizes SIZES>
 __global__ __launch_bounds__(kFusedThreads) void k_select_refit(PlanDesc P, int k_next) {
   __shared__ TopkSmem sm;
   __shared__ float mom[4][2];
@@ -224,7 +228,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_refit(PlanDesc P, int 
     P.ctrl[3] = P.ctrl[0] + 1u;
     P.ctrl[5] = 1u;
   }
-  topk_block<kFusedThreads, true>(P, sm, blockIdx.x == 0);
+  topk_block<kFusedThreads, true, SIZES>(P, sm, blockIdx.x == 0);
   if (c < 4 && t < P.T) {
     const int o = t * P.n + j;
     const auto row = gptr(P.U) + static_cast<size_t>(o) * static_cast<size_t>(P.ldU);
@@ -469,7 +473,8 @@ hipError_t launch_stage(const PlanDesc& P, int stage, int k, hipStream_t st) {
     case 1:
       return launch_rollout(P, st, -1);
     case 2:
-      k_topk<<<1, kTopkThreads, 0, st>>>(P);
+      if (topk_sizes(P) == kTopkSmall) k_topk<kTopkSmall><<<1, kTopkThreads, 0, st>>>(P);
+      else k_topk<kTopkLarge><<<1, kTopkThreads, 0, st>>>(P);
       if (P.diag & 1) {
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -584,8 +589,11 @@ static bool fuses_refit(const PlanDesc& P) {
 // 1024-thread selection (or its two launches) -> by one wave: 561 candidates x 3
 // links x 4 iterations 162.3 -> 152.6 us; 780 point masses x 6 140.4 -> 124.4 us;
 // 900 x 7 x 6 422 -> 406 us; 900 x 12 x 128 steps x 6 (384 tiles) 1057 -> 1034 us.
+// Not where the elites are a good part of the candidates: the short list that the
+// wave orders overflows then (64 of 128 candidates: a microsecond more an iteration).
 static bool selects_by_wave(const PlanDesc& P) {
-  return (P.diag & 1) == 0 && P.B <= 64 * kWaveKeys && P.E <= 64 && ((P.T + 3) / 4) * P.n <= 4 * P.gen_grid;
+  return (P.diag & 1) == 0 && P.B <= 64 * kWaveKeys && P.E <= 64 && 4 * P.E <= P.B &&
+         ((P.T + 3) / 4) * P.n <= 4 * P.gen_grid;
 }
 
 hipError_t launch_iteration(const PlanDesc& P, int k, int k0, int k1, hipStream_t st, const SideLane* side) {
@@ -603,10 +611,12 @@ hipError_t launch_iteration(const PlanDesc& P, int k, int k0, int k1, hipStream_
   if (by_wave) {
     if (ahead && !last) k_select_refit_wave<true><<<tiles, kUpdThreads, 0, st>>>(Pk, k + 1);
     else k_select_refit_wave<false><<<tiles, kUpdThreads, 0, st>>>(Pk, -1);
-  } else if (ahead && !last) {
-    k_select_refit<true><<<tiles, kFusedThreads, 0, st>>>(Pk, k + 1);
+  } else if (topk_sizes(P) == kTopkSmall) {
+    if (ahead && !last) k_select_refit<true, kTopkSmall><<<tiles, kFusedThreads, 0, st>>>(Pk, k + 1);
+    else k_select_refit<false, kTopkSmall><<<tiles, kFusedThreads, 0, st>>>(Pk, -1);
   } else {
-    k_select_refit<false><<<tiles, kFusedThreads, 0, st>>>(Pk, -1);
+    if (ahead && !last) k_select_refit<true, kTopkLarge><<<tiles, kFusedThreads, 0, st>>>(Pk, k + 1);
+    else k_select_refit<false, kTopkLarge><<<tiles, kFusedThreads, 0, st>>>(Pk, -1);
   }
   return hipGetLastError();
 }

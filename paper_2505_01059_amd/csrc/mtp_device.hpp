@@ -2244,14 +2244,40 @@ __device__ __forceinline__ const unsigned long long* topk_select(const PlanDesc&
   return ord;
 }
 
+// Batches of at most kTopkBoundary keys: every key counts the keys below it, and
+// that count is its place (189 keys, all of them elites: 0.6 us less than the
+// radix path; 561 keys 6 us more).
+template <int BS>
+__device__ __forceinline__ const unsigned long long* topk_select_small(const PlanDesc& P, TopkSmem& sm) {
+  static_assert(kTopkBoundary <= BS && kTopkBoundary <= kTopkRankSort, "a key per thread, and room for them");
+  const int tid = threadIdx.x, B = P.B;
+  unsigned long long key = 0ull;
+  if (tid < B) {
+    key = (static_cast<unsigned long long>(cost_order(gptr(P.cost)[tid])) << 32) | static_cast<uint32_t>(tid);
+    sm.keys[tid] = key;
+  }
+  __syncthreads();
+  if (tid < B) {
+    int rank = 0;
+#pragma unroll 8
+    for (int j = 0; j < B; ++j) rank += sm.keys[j] < key ? 1 : 0;
+    if (rank < P.E) sm.sorted[rank] = key;
+  }
+  return sm.sorted;
+}
+
 // KEEP: the elites' weights and indices stay in LDS (topk_weights, topk_elites)
 // for the refit of this workgroup, and only a `writer` workgroup stores them.
-template <int BS, bool KEEP = false>
+// SIZES: which of the two selections the kernel holds.
+enum TopkSizes { kTopkLarge, kTopkSmall, kTopkAnySize };
+template <int BS, bool KEEP = false, TopkSizes SIZES = kTopkAnySize>
 __device__ __forceinline__ void topk_block(const PlanDesc& P, TopkSmem& sm, bool writer = true) {
   const auto cost = gptr(P.cost);
   const int tid = threadIdx.x;
   const int B = P.B, E = P.E;
-  const unsigned long long* ord = topk_select<BS>(P, sm);
+  const unsigned long long* ord = SIZES == kTopkSmall || (SIZES == kTopkAnySize && B <= kTopkBoundary)
+                                      ? topk_select_small<BS>(P, sm)
+                                      : topk_select<BS>(P, sm);
   __syncthreads();
   // elites, costs and softmax weights w_e = exp(-(s_e - s_0)/lambda) / sum;
   // the unnormalised weights wait in LDS (the image cache is free by now)
