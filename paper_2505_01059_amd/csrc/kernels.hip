@@ -55,7 +55,11 @@ __global__ __launch_bounds__(kTopkThreads) void k_entropy(PlanDesc P, int k) {
 // tests, which this form issues once per candidate and step.  Replan on eight
 // lanes per candidate through the horizon before -> now: 3341 candidates x 77
 // steps x 6 iterations 0.170 -> 0.158 ms; 15700 x 256 x 6 0.477 -> 0.414 ms.
+// POINTS: see pm_tile_cost; a horizon of 16 or 32 steps fills one or two points of
+// each thread, and testing the obstacles for the idle ones as well cost up to 6 %
+// of a replan (12000 candidates x 16 steps, 30 obstacles).
 constexpr int kPmTileCands = 16;
+template <int POINTS>
 __global__ __launch_bounds__(kRollThreads) void k_rollout_point_mass(PlanDesc P) {
   if (static_cast<int>(blockIdx.x) >= P.roll_blocks) { gen_tensor_tiles(P); return; }
   __shared__ PmTile<kPmTileCands> tile;
@@ -69,7 +73,7 @@ __global__ __launch_bounds__(kRollThreads) void k_rollout_point_mass(PlanDesc P)
   const float* u = P.U + min(b0 + c, P.B - 1);
   constexpr int kRows = kRollThreads / kPmTileCands, kLoads = 2 * kTileSteps / kRows;
   const bool records = b0 < P.n_dbg;
-  const float cost = pm_tile_cost<kPmTileCands, kRollThreads>(
+  const float cost = pm_tile_cost<kPmTileCands, kRollThreads, POINTS>(
       P, tile, obs, n_pad,
       [&](int t0, int steps) {
         float v[kLoads];   // every load of the chunk in flight at once
@@ -107,6 +111,7 @@ __global__ __launch_bounds__(kRollThreads) void k_rollout_point_mass_lanes(PlanD
 // four iterations, tiles -> eight lanes: 18000 candidates x 20 steps, 30 obstacles
 // 11 % shorter, 39000 x 20 14 %, 18000 x 50, 8 obstacles 4 %, 18000 x 200 2 to 5 %;
 // 33000 x 200 1 % longer; 16000 x 50 12 % longer.
+static_assert(kPmPoints<kPmTileCands, kRollThreads> == 4 && kPmTileCands * 16 == kRollThreads, "a point per 16 steps");
 static_assert(kPmOverlapLanes == kPmLanes, "rollout_blocks counts the workgroups of the lanes");
 static bool pm_on_lanes(const PlanDesc& P) {
   constexpr int kTilesPerUnit = 4, kManyTiles = 7, kLongHorizon = 64;
@@ -394,7 +399,9 @@ template <bool ONE>
 static hipError_t launch_rollout_kernel(const PlanDesc& P, dim3 grid, size_t lds, hipStream_t st) {
   if (P.dyn == kPointMass) {
     if (pm_on_lanes(P)) k_rollout_point_mass_lanes<<<grid, kRollThreads, lds, st>>>(P);
-    else k_rollout_point_mass<<<grid, kRollThreads, lds, st>>>(P);
+    else if (P.T <= 16) k_rollout_point_mass<1><<<grid, kRollThreads, lds, st>>>(P);
+    else if (P.T <= 32) k_rollout_point_mass<2><<<grid, kRollThreads, lds, st>>>(P);
+    else k_rollout_point_mass<4><<<grid, kRollThreads, lds, st>>>(P);
     return hipGetLastError();
   }
   if (is_quad_chain(P.dyn, P.n_links)) return launch_rollout_quad(P, grid, lds, st, ONE);

@@ -44,8 +44,11 @@ __device__ __forceinline__ int load_obstacles(const PlanDesc& P, float4* obs) {
 // Costs of a tile of C candidates whose controls gen(t0, steps) writes to sm.u
 // chunk by chunk; rec(t, dim, cand, pos, vel) sees every state.  Every thread
 // of the workgroup (BS of them) calls this; the costs are returned on threads
-// 0 .. C - 1.
-template <int C, int BS, class Gen, class Rec>
+// 0 .. C - 1.  R: (candidate, step) points per thread, all of a chunk's unless the
+// horizon is shorter (pm_points).
+template <int C, int BS>
+constexpr int kPmPoints = kTileSteps * C / BS > 0 ? kTileSteps * C / BS : 1;
+template <int C, int BS, int R = kPmPoints<C, BS>, class Gen, class Rec>
 __device__ __forceinline__ float pm_tile_cost(const PlanDesc& P, PmTile<C>& sm, const float4* obs, int n_pad, Gen gen,
                                               Rec rec) {
   const int tid = threadIdx.x;
@@ -58,7 +61,6 @@ __device__ __forceinline__ float pm_tile_cost(const PlanDesc& P, PmTile<C>& sm, 
     pos = P.x0[dim];
     vel = P.x0[2 + dim];
   }
-  constexpr int R = kTileSteps * C / BS > 0 ? kTileSteps * C / BS : 1;   // points per thread
   for (int t0 = 0; t0 < P.T; t0 += kTileSteps) {
     const int steps = min(kTileSteps, P.T - t0);
     gen(t0, steps);

@@ -1,6 +1,6 @@
 """Point-mass rollouts on both sides of the choice between tiles and eight lanes per candidate, bit for bit those of the
-batched launch's one-lane form: the limits in horizon, obstacles and candidates, and one obstacle more than the lanes'
-registers hold."""
+batched launch's one-lane form: the limits in horizon, obstacles and candidates, one obstacle more than the lanes' registers
+hold, and the horizons that a tile's threads share out differently."""
 import numpy as np
 import pytest
 import torch
@@ -14,6 +14,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("total,horizon,obstacles,debug", [
     (16384, 20, 30, 0), (16385, 20, 30, 0), (16385, 20, 33, 0), (16385, 64, 8, 40), (16385, 96, 7, 0), (16385, 63, 0, 3),
     (28672, 64, 20, 0), (28673, 64, 20, 0), (28673, 63, 32, 0), (40001, 17, 25, 7), (17000, 7, 9, 0),
+    # one, two and four points of a chunk per thread of a tile
+    (900, 16, 20, 0), (900, 17, 30, 5), (900, 32, 20, 0), (900, 33, 9, 0), (900, 65, 20, 900), (8212, 1, 32, 0),
 ])
 def test_point_mass_rollout_equals_batched(total, horizon, obstacles, debug):
     cfg = W.point_mass_config(n_obstacles=obstacles, n_tensor=total - total // 9, n_gauss=total // 9, horizon=horizon,
