@@ -22,10 +22,13 @@ double wide_share(const PlanDesc& P, int lanes) {
 
 // A launch of `blocks` rollout workgroups, one per compute unit, each `wave_us`
 // long, with the generator if `gen`: on the units that the last round leaves, or
-// after it where these are too few.
-double launch_us(const PlanDesc& P, int blocks, double wave_us, bool gen) {
+// after it where these are too few.  `shared`: workgroups past the first round
+// share the units with others (the one-lane forms' registers admit it), so the
+// last round takes what there is of it.
+double launch_us(const PlanDesc& P, int blocks, double wave_us, bool gen, bool shared = false) {
   const int rounds = blocks / P.gen_grid, rest = blocks % P.gen_grid;
-  const double before = wave_us * rounds, last = rest > 0 ? wave_us : 0.0;
+  const double before = wave_us * rounds;
+  const double last = rest == 0 ? 0.0 : (shared && rounds > 0 ? wave_us * rest / P.gen_grid : wave_us);
   if (!gen) return before + last;
   const int left = P.gen_grid - rest;
   return before + (left >= kMinGenBlocks ? std::max(last, gen_us(P, left)) : last + gen_us(P, kMinGenBlocks));
@@ -67,7 +70,8 @@ double gen_us(const PlanDesc& P, int gens) {
 // us narrow, 620 on four lanes; 12 links 228 and 354; 28000 candidates of 4 links
 // on two lanes 261 and 341).  Randomised models side by side likewise: 18000
 // candidates of 24 links in contact, two models, 665 us in turn, 1042 side by
-// side.  Plain chains of two and three links stay narrow: moving three rows
+// side; but 45800 of 7 links in contact, two models x 128 steps, 888 us an iteration
+// in turn, 698 side by side, where workgroups share units.  Plain chains of two and three links stay narrow: moving three rows
 // across lanes costs what it saves (3 links, 561 candidates: 30.6 us narrow, 33.0
 // on four lanes).
 int wide_lanes(const PlanDesc& P, bool gen) {
@@ -83,7 +87,8 @@ int wide_lanes(const PlanDesc& P, bool gen) {
   for (int lanes = narrow; lanes <= most; lanes *= 2) {
     const int models = wide_models(lanes, P.R), passes = (P.R + models - 1) / models;
     if (lanes == narrow && P.R == 1) continue;   // the narrow form itself
-    const double us = launch_us(P, wide_blocks(P, lanes), wave * wide_share(P, lanes) * passes, gen);
+    const double us = launch_us(P, wide_blocks(P, lanes), wave * wide_share(P, lanes) * passes, gen,
+                                !pair && lanes == narrow);
     if (us < kGain * best_us) {
       best = lanes;
       best_us = us;

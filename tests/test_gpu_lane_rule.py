@@ -43,6 +43,7 @@ PAIRS = {
     "4 links": (_chain(4, W.LINEAR, 64), 28000, 29500),
     "24 links in contact": (_contact(24, 16, 1), 14000, 14600),
     "two models": (_contact(24, 16, 2), 14600, 28600),
+    "models that share units": (_contact(7, 24, 2), 32700, 45800),
     "7 links": (_chain(7, W.AKIMA, 128), 14000, 14600),
     "point mass": (_point_mass(64), 5000, 7300),
 }
