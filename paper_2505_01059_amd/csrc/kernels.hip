@@ -429,10 +429,11 @@ static hipError_t launch_rollout_kernel(const PlanDesc& P, dim3 grid, size_t lds
     // candidates x 96 steps 80.0 and 81.8, 40000 x 64 55.9 and 56.5; 2 links, 1100 x
     // 50 31.2 and 32.3, 20000 x 64 40.8 and 40.0.  Replans of four iterations with
     // the generator, 3 links, 600 x 32 154.4 and 152.5, 39000 x 16 260 and 250, 20000
-    // x 256 990 and 1015, but 55000 x 300, as long as its generator, 1539 and 1138.
+    // x 256 990 and 1015, but 55000 x 300, as long as its generator, 1539 and 1138; 2
+    // links, 73 x 200, five iterations 592 and 612.
     const bool alone = static_cast<int>(grid.x) == P.roll_blocks;
     const bool bound = !alone && gen_us(P, static_cast<int>(grid.x) - P.roll_blocks) > narrow_wave_us(P);
-    const bool here = P.n_links == 3 ? alone || (P.T >= 96 && !bound) : P.n_links == 2 && alone && P.B <= 8192;
+    const bool here = P.n_links <= 3 && (P.n_links == 3 || P.B <= 8192) && (alone || (P.T >= 96 && !bound));
     if (!here) return launch_rollout_line(P, grid, lds, st);
     switch (P.n_links) {
 #define X(N) case N: if constexpr (N <= 3) { k_rollout_chain<N, false, ONE><<<grid, kRollThreads, lds, st>>>(P); return hipGetLastError(); } break;
