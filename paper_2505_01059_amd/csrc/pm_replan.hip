@@ -414,7 +414,9 @@ hipError_t launch_pm_replan(const PlanDesc& P, uint32_t r, int shift, const floa
   if (P.K <= kPmChunk) return launch_range(P, r, shift, x0_src, P.K, WholeReplan{}, st);
   for (int k0 = 0; k0 < P.K; k0 += kPmChunk) {
     const int k1 = std::min(k0 + kPmChunk, P.K);
-    const hipError_t e = launch_range(P, r, shift, x0_src, k1 - k0, IterRange{k0, k1}, st);
+    // the caller's start state is read by the first kernel only, which keeps a copy
+    const float* x0 = k0 == 0 ? x0_src : P.x0;
+    const hipError_t e = launch_range(P, r, shift, x0, k1 - k0, IterRange{k0, k1}, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
