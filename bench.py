@@ -17,6 +17,10 @@ Prints one JSON line:
   roofline     the rollout kernel's algorithmic FP32 flops per launch over its
                mean launch time (HIP events around every rollout launch on the
                plan's stream, in a second timed pass launching kernels one by one);
+  stage_ms_per_launch
+               from the same pass.  The timed replans run selection and refit in
+               one kernel where that is faster, and small point masses whole in
+               kernels of their own: "stage_pass" says where the two differ;
   cpu_baseline the FP64 oracle on one CEM iteration of the workload (batches
                above 20000 candidates: a 1024-candidate subset), one thread;
                cpu_baseline_all_cores the same sample with its rollouts split
@@ -226,7 +230,7 @@ def main():
         "config": plan_info,
         "replans_per_s": rec["replans_per_s"],
         "latency_ms_p50": rec["latency_ms_p50"], "latency_ms_p99": rec["latency_ms_p99"],
-        "stage_ms_per_launch": rec["stage_ms_per_launch"],
+        "stage_ms_per_launch": rec["stage_ms_per_launch"], "stage_pass": rec["stage_pass"],
         "roofline": rec["roofline"],
     }
     if args.workload == "chain24_contact_bspline" and not args.no_secondary:
@@ -286,8 +290,17 @@ def time_plan(cfg, name, steps, warmup):
     p50 = statistics.median(lat)
     p99 = lat[min(len(lat) - 1, int(round(0.99 * (len(lat) - 1))))]
 
+    info = {"workload": name, "candidates": B, "tensor": cfg.n_tensor,
+            "gaussian": cfg.n_gauss, "horizon": T, "ctrl_dim": cfg.ctrl_dim,
+            "layers": cfg.n_layers, "width": cfg.n_width, "elites": cfg.n_elites,
+            "iters": K, "interp": W.INTERP_NAMES[int(cfg.interp)],
+            "overlap_tensor_paths": plan.draws_ahead()}
     # kernel timing pass: HIP events around every stage launch on the plan's stream
     plan.set_stage_timing(True)
+    # a plan that draws ahead stage by stage but not in its default mode runs whole there
+    whole = plan.draws_ahead() and not info["overlap_tensor_paths"]
+    stage_pass = ("staged kernels; the timed replans run other kernels (whole point-mass replans)" if whole else
+                  "one launch per stage; the timed replans may run selection and refit in one")
     for _ in range(steps):
         plan.replan(x0_dev, shift=1)
     torch.cuda.synchronize()
@@ -306,15 +319,10 @@ def time_plan(cfg, name, steps, warmup):
         "flops_per_sample_step": flops_step, "launch_ms": round(roll_avg_ms, 4),
         "frac_of_unpacked_fp32": round(achieved / RF.PEAK_FP32_UNPACKED_TFLOPS, 4),
     }
-    info = {"workload": name, "candidates": B, "tensor": cfg.n_tensor,
-            "gaussian": cfg.n_gauss, "horizon": T, "ctrl_dim": cfg.ctrl_dim,
-            "layers": cfg.n_layers, "width": cfg.n_width, "elites": cfg.n_elites,
-            "iters": K, "interp": W.INTERP_NAMES[int(cfg.interp)],
-            "overlap_tensor_paths": plan.draws_ahead()}
     rec = {"rollout_steps_per_s": B * T * K * steps / wall, "ms_per_replan": ms_per_step,
            "replans_per_s": steps / wall, "latency_ms_p50": round(p50, 4), "latency_ms_p99": round(p99, 4),
            "stage_ms_per_launch": {k: round(v[0] / max(v[1], 1), 4) for k, v in st.items()},
-           "roofline": roofline}
+           "stage_pass": stage_pass, "roofline": roofline}
     plan.close()
     return rec, info
 

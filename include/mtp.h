@@ -214,12 +214,17 @@ mtp_status mtp_run_stage(mtp_plan* p, int32_t stage, uint32_t replan_idx, int32_
 mtp_status mtp_set_x0(mtp_plan* p, const float* d_x0);
 
 /* How Alg. 2's planning step is launched (the arithmetic is the same): replay
- * a captured hipGraph (1, default) or launch kernels one by one (0). */
+ * a captured hipGraph (1, default) or launch kernels one by one (0).  In the
+ * default mode point masses of at most 1024 candidates, 32 of them local, and 64
+ * elites run whole replans in two kernels of their own per 64 iterations, without a
+ * graph; both modes run selection and refit in one kernel where that is faster. */
 mtp_status mtp_set_graph_mode(mtp_plan* p, int32_t use_graph);
 
 /* Measurement of Alg. 2's stages (no arithmetic of its own): per-stage kernel
  * timing with hipEvents recorded on the plan's stream around every
- * stage launch.  While enabled, replans launch their kernels one by one (no graph).
+ * stage launch.  While enabled, replans launch their kernels one by one (no graph),
+ * one launch per stage: selection and refit apart, small point masses stage by
+ * stage, so the stages' sum can exceed the replan of the other modes.
  * mtp_get_stage_times waits for the recorded events and returns, per stage
  * (candidates, rollout, top-E, refit), the summed kernel milliseconds and the
  * number of launches since timing was enabled. */
@@ -229,11 +234,12 @@ mtp_status mtp_get_stage_times(mtp_plan* p, double* h_ms4, uint64_t* h_count4);
 /* Device views of the intermediates of Alg. 2's last loop body (layouts above). */
 mtp_status mtp_get_buffers(const mtp_plan* p, mtp_buffers* out);
 
-/* 1 if the plan draws each next CEM iteration's tensor-path controls during the
- * current iteration's rollout, else 0 (decided at creation from the config: more
- * than one iteration, tensor paths drawn with replacement, and a
+/* 1 if the plan, in its present launch mode, draws each next CEM iteration's
+ * tensor-path controls during the current iteration's rollout, else 0 (from the
+ * config: more than one iteration, tensor paths drawn with replacement, and a
  * rollout grid that leaves at least 32 of the 256 compute units free; on a
- * device with fewer units than that the plan runs the plain sequence).  Such a
+ * device with fewer units than that the plan runs the plain sequence; 0 where the
+ * default mode runs small point masses whole, see mtp_set_graph_mode).  Such a
  * plan's workspace holds a second [T][n][ldU] candidate buffer; the U buffer of
  * mtp_get_buffers still holds the candidates of the last iteration run.  The
  * results are the same bits either way (Alg. 2: the tensor paths do not depend

@@ -343,7 +343,7 @@ class Plan:
         _check(self.lib, self.lib.mtp_run_stage(self.handle, int(stage), int(replan_idx), int(k)), self.handle)
 
     def draws_ahead(self):
-        """Whether each rollout also draws the next iteration's tensor-path controls."""
+        """Whether, in the present launch mode, each rollout also draws the next iteration's tensor-path controls."""
         return bool(self.lib.mtp_plan_draws_ahead(self.handle))
 
     def set_graph_mode(self, on):

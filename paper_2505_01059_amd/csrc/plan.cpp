@@ -252,6 +252,14 @@ struct mtp_plan {
   std::string err;
 };
 
+// Whether replans run as the kernels of pm_replan.hip in the present launch mode.
+static bool runs_whole(const mtp_plan* p) { return p->lay.pm && p->use_graph && !p->timing; }
+
+// Whether the staged replans draw each next iteration's tensor paths ahead.
+static bool staged_draws_ahead(const mtp_plan* p) {
+  return p->lay.overlap && (p->lay.segmented || p->P.gen_grid > rollout_blocks(p->P));
+}
+
 static mtp_status set_err(mtp_plan* p, mtp_status s, const std::string& msg) {
   if (p) p->err = msg;
   return s;
@@ -587,7 +595,7 @@ mtp_status mtp_plan_create(const mtp_config* cfg, void* d_workspace, size_t ws_b
   }
   // with an even iteration count the last iteration's generator writes the
   // buffer that the next replan's iteration 0 reads
-  p->P.spec = (mtp_plan_draws_ahead(p) && cfg->n_iters % 2 == 0) ? 1 : 0;
+  p->P.spec = (staged_draws_ahead(p) && cfg->n_iters % 2 == 0) ? 1 : 0;
   *out = p;
   return MTP_OK;
 }
@@ -615,7 +623,7 @@ mtp_status mtp_replan_at(mtp_plan* p, const float* d_x0, int32_t shift_steps, ui
   if (d_x0 == nullptr) return set_err(p, MTP_ERR_INVALID_ARG, "d_x0 is NULL");
   if (shift_steps < 0) return set_err(p, MTP_ERR_INVALID_ARG, "shift_steps must be >= 0");
   const bool graph = p->use_graph && !p->timing;
-  if (graph && p->lay.pm) {
+  if (runs_whole(p)) {
     HIPCHK(p, launch_pm_replan(p->P, replan_idx, shift_steps, d_x0, p->stream), "point-mass replan");
     p->next_r = replan_idx + 1;
     return MTP_OK;
@@ -692,7 +700,7 @@ mtp_status mtp_run_stage(mtp_plan* p, int32_t stage, uint32_t replan_idx, int32_
 }
 
 int32_t mtp_plan_draws_ahead(const mtp_plan* p) {
-  return (p != nullptr && p->lay.overlap && (p->lay.segmented || p->P.gen_grid > rollout_blocks(p->P))) ? 1 : 0;
+  return (p != nullptr && staged_draws_ahead(p) && !runs_whole(p)) ? 1 : 0;
 }
 
 mtp_status mtp_set_graph_mode(mtp_plan* p, int32_t use_graph) {
