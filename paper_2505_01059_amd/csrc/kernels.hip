@@ -216,8 +216,8 @@ __global__ __launch_bounds__(kUpdThreads) void k_refit_regen(PlanDesc P, int k, 
 // step each, as k_update, or k_update_next with NEXT.  The selection is one
 // workgroup's latency either way, and one launch less is a microsecond per
 // iteration.  Replans in two launches -> one (candidates x links x iterations):
-// 9216 x 7 x 8 1.020 -> 1.002 ms; 3376 x 12 x 6 0.631 -> 0.621 ms; 3341 point
-// masses x 6 153.3 -> 146.2 us; 13500 x 4 x 4 0.310 -> 0.303 ms.
+// 9216 x 7 x 8 1.014 -> 0.994 ms; 3376 x 12 x 6 0.632 -> 0.621 ms; 3341 point
+// masses x 6 157.7 -> 152.8 us; 13500 x 4 x 4 0.310 -> 0.303 ms.
 constexpr int kFusedThreads = kTopkThreads;
 template <bool NEXT, TopkSizes SIZES>
 __global__ __launch_bounds__(kFusedThreads) void k_select_refit(PlanDesc P, int k_next) {
@@ -361,8 +361,8 @@ static size_t gen_lds_bytes(const PlanDesc& P) { return std::max(gen_tile_bytes(
 template <bool ONE>
 static hipError_t launch_rollout_kernel(const PlanDesc& P, dim3 grid, size_t lds, hipStream_t st);
 
-// The rollout of P.U; with gen_k >= 0 the launch adds workgroups up to
-// P.gen_grid that draw iteration gen_k's tensor-path controls into P.U2.
+// The rollout of P.U; with gen_k >= 0 the launch adds workgroups that draw
+// iteration gen_k's tensor-path controls into P.U2.
 static hipError_t launch_rollout(const PlanDesc& P0, hipStream_t st, int gen_k) {
   PlanDesc P = P0;
   if (is_pair_chain(P.dyn, P.n_links) && P.seg_ctl != nullptr && P.seg_grid > 0) return launch_rollout_seg(P, st);

@@ -145,7 +145,8 @@ __device__ __forceinline__ void store_agent(T* p, T v) {
 
 // Costs, moments and action: at agent scope where they are read or written again
 // by other compute units within the launch (the batched launch, which sets
-// MTP_SHARED_LAUNCH), else plain stores, which end sooner (561 candidates x 3 links: 163.2 us per replan, 166.8 at agent scope).
+// MTP_SHARED_LAUNCH), else plain stores, which end sooner (561 candidates x 3
+// links: 163.2 us per replan, 166.8 at agent scope).
 #ifndef MTP_SHARED_LAUNCH
 #define MTP_SHARED_LAUNCH 0
 #endif
@@ -154,7 +155,14 @@ __device__ __forceinline__ void store_result(float* p, float v) {
   else *gptr(p) = v;
 }
 
-// Waits until this wave's stores have reached memory.
+// Waits until this wave's stores have reached memory.  What follows in the wave, a
+// flag or a count stored or added at agent scope, is then seen after them, though
+// neither is a release: gfx950 counts a store in vmcnt until it is acknowledged,
+// and one at agent scope is acknowledged past the L2 that it would have to be
+// written back from, where every XCD reads (loads of a flag's data are issued after
+// the flag's value has come back, and go past the L2 or follow an invalidation).
+// The language's memory model promises none of this, so it holds for this target
+// alone; the compiler barriers keep the order of the instructions.
 __device__ __forceinline__ void stores_done() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vector memory
@@ -1652,8 +1660,9 @@ __device__ __forceinline__ void rollout_chain_pair(const PlanDesc& P, int b, boo
 // rounds of work).  Here the horizon is cut into S segments and resident waves
 // take (wave group, segment) units from a counter in segment-major order, saving
 // the group's state (angles, rates, cost so far) between segments; a unit waits
-// for its group's previous segment, taken at least one full round earlier.  The
-// arithmetic per candidate is exactly that of the plain rollout.
+// for its group's previous segment, which was taken `groups` units earlier, by then
+// done or in another wave's hands (no more waves than groups).  The arithmetic per
+// candidate is exactly that of the plain rollout.
 
 struct SegCtl {
   uint32_t head;     // next unit
@@ -2458,9 +2467,9 @@ __device__ __forceinline__ void entropy_block(const PlanDesc& P, int k, EntropyS
 // the second pass would double the line traffic); larger elite sets re-read.
 constexpr int kUpdKeep = 16;
 
-// Refits output o = (t, j); every lane returns the new mean and std, lane 0 stores them.
-// The refit of output o from the elites' controls val(e) (e < E), with
-// weights w[e] in a fixed order: weighted mean, weighted variance about it, sigma floor, smoothing.
+// Refit of output o = (t, j) from the elites' controls val(e) (e < E) with weights
+// w[e], in a fixed order: weighted mean, weighted variance about it, sigma floor,
+// smoothing.  Every lane returns the new mean and std, lane 0 stores them.
 template <class Weights, class Val>
 __device__ __forceinline__ void update_output_from(const PlanDesc& P, int o, Weights w, Val val, float* mu_new,
                                                    float* sg_new) {
