@@ -803,7 +803,7 @@ mtp_status mtp_batch_get_schedule(const mtp_batch* b, mtp_batch_schedule* h_sche
 
 mtp_status mtp_batch_item_shapes(const mtp_config* cfgs, int32_t n, int32_t workgroups,
                                  const mtp_batch_schedule* h_schedule, uint64_t queue_items, mtp_batch_items* h_out) {
-  if (cfgs == nullptr || n < 1 || workgroups < 1 || h_schedule == nullptr || h_out == nullptr ||
+  if (cfgs == nullptr || n < 1 || n > 65536 || workgroups < 1 || h_schedule == nullptr || h_out == nullptr ||
       !schedule_valid(*h_schedule))
     return MTP_ERR_INVALID_ARG;
   std::vector<LaunchPart> parts(n);

@@ -1,9 +1,12 @@
 """Item shapes of the batched launch (host only): finer items and wide rollout tiles are taken where the estimate of an
 instance's path says that they are shorter, never where they only add work."""
+import ctypes
+
 import pytest
 
 import mtp_workloads as W
 import paper_2505_01059_amd as mtp
+from paper_2505_01059_amd import _native as N
 
 UNITS = 256
 
@@ -79,6 +82,12 @@ def test_a_short_queue_takes_back_only_what_does_not_fit(name):
 
 
 def test_bad_arguments_are_refused():
+    lib = mtp.load()
+    assert lib.mtp_batch_item_shapes(None, 1, UNITS, None, 0, None) == 1
+    cfg, keep = mtp.config_struct(SETS["small"][0])
+    s, out = N.mtp_batch_schedule(0, 1, 1, 1, 64, 100), N.mtp_batch_items()
+    for n in (0, 65537):   # as many as a batch takes
+        assert lib.mtp_batch_item_shapes(ctypes.byref(cfg), n, UNITS, ctypes.byref(s), 0, ctypes.byref(out)) == 1
     with pytest.raises(mtp.MtpError):
         mtp.batch_item_shapes(SETS["small"], 0)
     with pytest.raises(mtp.MtpError):
