@@ -70,10 +70,10 @@ double gen_us(const PlanDesc& P, int gens) {
 // us narrow, 620 on four lanes; 12 links 228 and 354; 28000 candidates of 4 links
 // on two lanes 261 and 341).  Randomised models side by side likewise: 18000
 // candidates of 24 links in contact, two models, 665 us in turn, 1042 side by
-// side; but 45800 of 7 links in contact, two models x 128 steps, 888 us an iteration
-// in turn, 698 side by side, where workgroups share units.  Plain chains of two and three links stay narrow: moving three rows
-// across lanes costs what it saves (3 links, 561 candidates: 30.6 us narrow, 33.0
-// on four lanes).
+// side; but 45800 of 7 links in contact, two models x 128 steps, 888 us an
+// iteration in turn, 698 side by side, where workgroups share units.  Plain chains
+// of two and three links stay narrow: moving three rows across lanes costs what it
+// saves (3 links, 561 candidates: 30.6 us narrow, 33.0 on four lanes).
 int wide_lanes(const PlanDesc& P, bool gen) {
   if (P.dyn == kPointMass || is_quad_chain(P.dyn, P.n_links)) return 0;
   const bool pair = is_pair_chain(P.dyn, P.n_links);
